@@ -37,9 +37,10 @@
 //    SIMD.
 //
 // 2. Per setting l: omega^phase8 sqrt(2)^pow * prod_k h(alpha_k, beta_k;
-//    a_kl, b_kl), h of equation phase_pair, phases multiples of pi/4.  One
-//    lane per setting, fp32 complex products, renormalised to a power of two
-//    every 8 factors.
+//    a_kl, b_kl), h of equation phase_pair, phases multiples of pi/4.  Terms
+//    whose values are all 2 i^s are counted bit-sliced; with any other term,
+//    one lane per setting, fp32 complex products, renormalised to a power of
+//    two every 8 factors.
 #include "zx_internal.h"
 
 namespace {
@@ -539,7 +540,8 @@ __global__ __launch_bounds__(M2_BS, 2) void gf2mm_tile2_kernel(MmArgs a) {
 
 // ------------------------------------------------------ phase-pair product --
 
-constexpr int PP_BS = 256;
+constexpr int PP_BS = 256;      // settings per workgroup (four words of a row)
+constexpr int PP_T = 1024;      // threads per workgroup
 constexpr int PP_CHUNK = 256;   // terms whose h tables sit in LDS at a time
 constexpr float RH = 0.70710678118654752440f;
 
@@ -567,18 +569,46 @@ __device__ __forceinline__ void renorm(float2& z, int& e) {
   e += ex;
 }
 
-__global__ __launch_bounds__(PP_BS) void phase_pair_kernel(const uint64_t* __restrict__ A,
+// A term is a unit term when each of its four values h(k; a, b) is 2 i^s: both
+// codes even and one of them 0 or 4 (the two kinds that the rewrite rules
+// leave, (0 or 4, 2) and (0 or 4, 0 or 4), are).  With that code first, h = 2
+// if its phase comes out 0 and 2 e^{i beta'} if it comes out pi.
+__device__ __forceinline__ bool unit_term(int ka, int kb) { return ((ka | kb) & 1) == 0 && ((ka & 3) == 0 || (kb & 3) == 0); }
+
+// One block: 256 settings (four words of every row of A and B).
+//
+// Unit terms only: the product is 2^m i^(sum of s), so the settings need one
+// two-bit counter each, kept bit-sliced over a word's 64 settings.  Thread
+// (slice, word) adds the terms slice, slice + 256, ...; the 256 partial
+// counters are added by lane swaps and once through LDS.  Products by 2 i^s
+// are exact in fp32, so mantissa and exponent are those of the factor-by-
+// factor product.  Bound: reading A and B once; 16 wavefronts a CU keep the
+// loads in flight (46 us with four).
+//
+// Any other term: the factor-by-factor product, one lane per setting, the
+// term's words and h values from LDS (256 terms at a time), eight terms'
+// reads in flight.  Bound: ten VALU operations per term and setting.
+//
+// 4096 terms x 65536 settings: 1190 us with one dependent scalar load chain
+// per term -> 20 us (unit terms), 160 us (any codes).
+__global__ __launch_bounds__(PP_T) void phase_pair_kernel(const uint64_t* __restrict__ A,
                                                            const uint64_t* __restrict__ B, int64_t ld,
                                                            int32_t m, int64_t n_set,
                                                            const int8_t* __restrict__ ka,
                                                            const int8_t* __restrict__ kb, int32_t phase8,
                                                            int64_t pow_sqrt2, float2* __restrict__ mant,
                                                            int32_t* __restrict__ expo) {
-  __shared__ float2 tab[PP_CHUNK][4];  // h(k; a, b) at index a + 2 b
-  const int64_t l = (int64_t)blockIdx.x * PP_BS + threadIdx.x;
-  // uniform over the wave: the term words are scalar loads
-  const int64_t wcol = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * PP_BS + (threadIdx.x & ~63)) >> 6));
-  const int bitpos = (int)(l & 63);
+  __shared__ float2 tab[PP_CHUNK][4];       // h(k; a, b) at index a + 2 b
+  __shared__ uint2 bits[PP_CHUNK][PP_BS / 32];  // 32 settings' bits of A's row and of B's
+  __shared__ uint64_t part[PP_T / 64][4][2];    // the waves' counters
+  __shared__ int odd_wave[PP_T / 64];           // a wave saw a term that is no unit term
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  // neighbouring blocks share cache lines of the rows: runs of them on one XCD
+  const int64_t nb = (n_set + PP_BS - 1) / PP_BS, per = (nb + 7) / 8;
+  const int64_t blk = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if ((int64_t)(blockIdx.x >> 3) >= per || blk >= nb) return;
+  const int64_t l = blk * PP_BS + tid;
+  const int64_t nw = (n_set + 63) / 64, w0 = blk * (PP_BS / 64);
   // c = omega^phase8 sqrt(2)^pow
   const bool odd = (pow_sqrt2 & 1) != 0;
   int e = (int)((pow_sqrt2 - (odd ? 1 : 0)) / 2);
@@ -588,28 +618,93 @@ __global__ __launch_bounds__(PP_BS) void phase_pair_kernel(const uint64_t* __res
     z.y *= 1.41421356237309504880f;
   }
   renorm(z, e);
-  for (int k0 = 0; k0 < m; k0 += PP_CHUNK) {
-    const int nk = m - k0 < PP_CHUNK ? m - k0 : PP_CHUNK;
-    __syncthreads();
-    for (int x = threadIdx.x; x < nk * 4; x += PP_BS) {
-      const int k = x >> 2, ab = x & 3, av = ab & 1, bv = ab >> 1;
-      const int ak = ka[k0 + k], bk = kb[k0 + k];
-      const float2 p = omega_pow(ak + 4 * av), q = omega_pow(bk + 4 * bv), r = omega_pow(ak + bk + 4 * av + 4 * bv);
-      tab[k][ab] = make_float2(1.0f + p.x + q.x - r.x, p.y + q.y - r.y);
+
+  // bit-sliced sum of s over this thread's terms
+  uint64_t c0 = 0, c1 = 0;
+  bool other = false;
+  {
+    const int64_t w = w0 + (tid & 3) < nw ? w0 + (tid & 3) : nw - 1;
+    const int slice = tid >> 2;
+    const uint64_t* pa = A + w;
+    const uint64_t* pb = B + w;
+#pragma unroll 4
+    for (int k = slice; k < m; k += PP_T / 4) {
+      const int ak = ka[k] & 7, bk = kb[k] & 7;
+      const uint64_t aw = pa[(int64_t)k * ld], bw = pb[(int64_t)k * ld];
+      other |= !unit_term(ak, bk);
+      const bool swap = (ak & 3) != 0;  // B's code is the one in {0, 4}
+      const int f = swap ? bk : ak, g = swap ? ak : bk;
+      const uint64_t on = (swap ? bw : aw) ^ (uint64_t)(int64_t)(-(f >> 2));  // settings whose s is not 0
+      const uint64_t hi = (swap ? aw : bw) ^ (uint64_t)(int64_t)(-(g >> 2));
+      const uint64_t lo = on & (uint64_t)(int64_t)(-((g >> 1) & 1));
+      c1 ^= (on & hi) ^ (c0 & lo);
+      c0 ^= lo;
     }
-    __syncthreads();
-    if (l < n_set) {
-      for (int k = 0; k < nk; ++k) {
-        const uint64_t aw = A[(int64_t)(k0 + k) * ld + wcol];
-        const uint64_t bw = B[(int64_t)(k0 + k) * ld + wcol];
-        const int idx = (int)((aw >> bitpos) & 1) + 2 * (int)((bw >> bitpos) & 1);
-        z = cmul(z, tab[k][idx]);
-        if ((k & 7) == 7) renorm(z, e);
+  }
+#pragma unroll
+  for (int d = 4; d < 64; d <<= 1) {  // the 16 slices of the wave
+    const uint64_t o0 = (uint64_t)__shfl_xor((long long)c0, d), o1 = (uint64_t)__shfl_xor((long long)c1, d);
+    c1 ^= o1 ^ (c0 & o0);
+    c0 ^= o0;
+  }
+  const uint64_t any_other = __ballot(other);
+  if (lane < 4) {
+    part[wv][lane][0] = c0;
+    part[wv][lane][1] = c1;
+  }
+  if (lane == 0) odd_wave[wv] = any_other != 0;
+  __syncthreads();
+  int general = 0;
+#pragma unroll
+  for (int v = 0; v < PP_T / 64; ++v) general |= odd_wave[v];
+
+  if (!general) {
+    // this thread's setting: bit lane of word wv
+    if (tid >= PP_BS) return;
+    uint32_t s = 0;
+#pragma unroll
+    for (int v = 0; v < PP_T / 64; ++v)
+      s += (uint32_t)((part[v][wv][0] >> lane) & 1) + 2u * (uint32_t)((part[v][wv][1] >> lane) & 1);
+    if (s & 1) z = make_float2(-z.y, z.x);
+    if (s & 2) z = make_float2(-z.x, -z.y);
+    e += m;
+  } else {
+    for (int k0 = 0; k0 < m; k0 += PP_CHUNK) {
+      const int nk = m - k0 < PP_CHUNK ? m - k0 : PP_CHUNK;
+      __syncthreads();
+      for (int x = tid; x < nk * 4; x += PP_T) {
+        const int k = x >> 2, ab = x & 3, av = ab & 1, bv = ab >> 1;
+        const int ak = ka[k0 + k], bk = kb[k0 + k];
+        const float2 p = omega_pow(ak + 4 * av), q = omega_pow(bk + 4 * bv), r = omega_pow(ak + bk + 4 * av + 4 * bv);
+        tab[k][ab] = make_float2(1.0f + p.x + q.x - r.x, p.y + q.y - r.y);
+        const int64_t w = w0 + ab < nw ? w0 + ab : nw - 1;
+        const uint64_t aw = A[(int64_t)(k0 + k) * ld + w], bw = B[(int64_t)(k0 + k) * ld + w];
+        bits[k][2 * ab] = make_uint2((uint32_t)aw, (uint32_t)bw);
+        bits[k][2 * ab + 1] = make_uint2((uint32_t)(aw >> 32), (uint32_t)(bw >> 32));
+      }
+      __syncthreads();
+      if (tid >= PP_BS) continue;  // staging only
+      const int col = tid >> 5, sh = tid & 31;
+      int k = 0;
+      for (; k + 8 <= nk; k += 8) {
+        float2 hv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const uint2 ab = bits[k + u][col];
+          hv[u] = tab[k + u][((ab.x >> sh) & 1) + 2 * ((ab.y >> sh) & 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) z = cmul(z, hv[u]);
+        renorm(z, e);
+      }
+      for (; k < nk; ++k) {
+        const uint2 ab = bits[k][col];
+        z = cmul(z, tab[k][((ab.x >> sh) & 1) + 2 * ((ab.y >> sh) & 1)]);
       }
       renorm(z, e);
     }
   }
-  if (l < n_set) {
+  if (tid < PP_BS && l < n_set) {
     if (z.x == 0.0f && z.y == 0.0f) e = 0;
     mant[l] = z;
     expo[l] = e;
@@ -738,9 +833,9 @@ extern "C" zx_status zx_phase_pair_product(const uint64_t* A, const uint64_t* B,
   ZX_CHECK_ARG(n_terms == 0 || (A && B && k_alpha && k_beta), "null term input");
   ZX_CHECK_ARG(n_terms == 0 || ld >= (n_settings + 63) / 64, "ld below %lld words",
                (long long)((n_settings + 63) / 64));
-  const int64_t blocks = (n_settings + PP_BS - 1) / PP_BS;
+  const int64_t blocks = ((n_settings + PP_BS - 1) / PP_BS + 7) / 8 * 8;  // whole runs per XCD
   ZX_CHECK_ARG(blocks <= 0x7fffffff, "too many settings");
-  hipLaunchKernelGGL(phase_pair_kernel, dim3((unsigned)blocks), dim3(PP_BS), 0, s, A, B, ld, n_terms,
+  hipLaunchKernelGGL(phase_pair_kernel, dim3((unsigned)blocks), dim3(PP_T), 0, s, A, B, ld, n_terms,
                      n_settings, k_alpha, k_beta, phase8 & 7, pow_sqrt2, (float2*)mant, expo);
   ZX_HIP(hipGetLastError());
   return ZX_OK;

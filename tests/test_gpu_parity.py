@@ -87,3 +87,31 @@ def test_phase_pair_product_matches_oracle(zx, seed, m, n):
                                    phase8, pw)
     torch.cuda.synchronize()
     _compare(mg.cpu().numpy(), eg.cpu().numpy(), mo, eo, m)
+
+
+@pytest.mark.parametrize("m,n", [(1, 1), (2, 63), (63, 64), (64, 65), (65, 255), (129, 256), (257, 257), (600, 2050)])
+@pytest.mark.parametrize("last", ["unit", "any"])
+def test_phase_pair_unit_terms(zx, m, n, last):
+    """Terms whose factors are all 2 i^s (even codes, one of them 0 or 4) are
+    counted and not multiplied: edges of the 64-term slices and of the
+    256-setting blocks, either code first, both parities present.  The
+    product is then exact but for the constant (tolerance of no factor at
+    all).  With one other term at the end the whole product is multiplied
+    out (tolerance of m factors)."""
+    import torch
+    print("phase_pair unit case", m, n, last, flush=True)
+    rng = np.random.default_rng(900 + 31 * m + n)
+    ka = 4 * rng.integers(0, 2, m)
+    kb = 2 * rng.integers(0, 4, m)
+    swap = rng.random(m) < 0.5
+    ka, kb = np.where(swap, kb, ka).astype(np.int8), np.where(swap, ka, kb).astype(np.int8)
+    if last == "any":
+        ka[-1] = 3
+    A = pack_rows((rng.random((m, n)) < 0.5).astype(np.uint8))
+    B = pack_rows((rng.random((m, n)) < 0.5).astype(np.uint8))
+    phase8, pw = int(rng.integers(0, 8)), int(rng.integers(-9, 10))
+    mo, eo = oph.phase_pair_product(A, B, ka, kb, n, phase8, pw)
+    mg, eg = zx.phase_pair_product(zx.to_device_words(A), zx.to_device_words(B), torch.from_numpy(ka).cuda(),
+                                   torch.from_numpy(kb).cuda(), n, phase8, pw)
+    torch.cuda.synchronize()
+    _compare(mg.cpu().numpy(), eg.cpu().numpy(), mo, eo, 0 if last == "unit" else m)
