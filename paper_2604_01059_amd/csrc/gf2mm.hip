@@ -11,30 +11,26 @@
 //    (E2M1) values: a set bit is the code 0b0001 (0.5), the block scale 2^1
 //    makes it 1.0, so every product is 0 or 1 and the fp32 sums (at most the
 //    row length, far below 2^24) are exact counts; bit 0 of the count is the
-//    parity.  Unpacking a 32-bit word of bits costs seven VALU operations:
-//    nibble r of dword t of the operand holds bit 4r + t of the word, i.e.
-//    operand dword t = (word >> t) & 0x11111111.  The order in which bits
-//    reach the k positions of the instruction does not matter, since A and
-//    B fragments are unpacked the same way and the sum runs over all k.
+//    parity.  Bits are unpacked by bit plane: plane t of four consecutive
+//    dwords (bits 4r + t) is an operand as it stands, d & (0x11111111 << t).
 //
-//    Two tilings.  The symmetric table (and K beyond 2048 bits): one
-//    persistent workgroup of 512 threads per CU walking 256 x 256 output
-//    tiles, each wavefront a 64 x 128 part (2 x 4 blocks of 32 x 32, 128
-//    fp32 accumulators per lane, two wavefronts per SIMD).  The rows' bits go through LDS in chunks of
-//    256 bits (4 words, double buffered): 16 KiB per chunk for the 512 rows
-//    of the tile; the next chunk's rows are loaded while a chunk is
-//    multiplied, across tile boundaries too.  For each 64-bit step of a
-//    chunk, lane half h of a fragment takes dword 4h + s of its row's chunk.
-//    General products with K up to 2048 bits: 128 x 128 tiles whose rows are
-//    staged whole (below), two workgroups per CU.  Parities leave through
-//    wave ballots (row words) and, for the symmetric table, through per-lane
-//    packing (the mirrored tile's row words).  Tiles are dealt to the eight
-//    XCDs in contiguous runs of the tile order, so one XCD's tiles share rows
-//    in its L2.  Row loads are branch-free (the compiler otherwise waits for
-//    each load before issuing the next).  65536-string table: 5.25 ms with
-//    one wavefront per SIMD, per-tile workgroups and branching loads; 3.96
-//    ms persistent with branch-free loads; 2.79 ms with two wavefronts per
-//    SIMD.
+//    One persistent kernel, 256 x 256 or 128 x 128 output tiles; a wavefront
+//    owns 64 x 128 (64 x 64) of a tile: 2 x 4 blocks of 32 x 32, 128 fp32
+//    accumulators per lane, two wavefronts per SIMD.  Rows go through LDS in
+//    chunks of 512 bits, double buffered, the next chunk's loads in flight
+//    during a chunk's products and across tiles.  B's rows are the
+//    instruction's first operand, so that a lane's accumulators are
+//    neighbouring columns of one row of C: one funnel shift each packs the
+//    parities, and the mirrored half of the symmetric table is a transpose of
+//    32 x 32 bit blocks across lanes.  (With A's rows first, 16 ballots a
+//    block and as many LDS writes gathered the row words: as many VALU cycles
+//    as the products took.)
+//
+//    Bound: the matrix cores.  65536-string table, 1024 qubits: 2.49 -> 1.50
+//    ms (5.9 PFLOP/s; the instruction with this unpacking and nothing else
+//    reaches 7.7 PFLOP/s at the clock the card holds); 4096 x 65536 x 1024
+//    bits: 196 -> 112 us (4.9 PFLOP/s).  The rest is the parity write-out
+//    (about 10 %) and the row loads (about 10 %).
 //
 // 2. Per setting l: omega^phase8 sqrt(2)^pow * prod_k h(alpha_k, beta_k;
 //    a_kl, b_kl), h of equation phase_pair, phases multiples of pi/4.  Terms
@@ -50,200 +46,198 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 #define LDS __attribute__((address_space(3)))
 
-// Waves per workgroup of the 256 x 256 kernel: 8 (each a 64 x 128 part, 128
-// accumulators, two waves per SIMD, so one wave's operand unpacking and
-// loads overlap the other's products): 2.79 ms for the 65536-string table
-// against 3.76 ms with 4 (each a 128 x 128 quarter, one wave per SIMD).
-constexpr int MM_NW = 8;
-constexpr int MM_T = 256;     // output tile edge
-constexpr int MM_CW = 4;      // words per chunk
-constexpr int SCALE_ONE = 128;  // E8M0 2^1: FP4 code 0b0001 (0.5) scaled to 1.0
+constexpr int MM_W = 8;  // words of a row staged at a time (two 256-bit groups)
 
 struct MmArgs {
-  const uint64_t* a0;  // row i of A = a0 row i (kw0 words) then a1 row i (kw1 words)
-  const uint64_t* a1;
-  const uint64_t* b0;  // row j of B = b0 row j (kw0 words) then b1 row j (kw1 words)
-  const uint64_t* b1;
-  int64_t lda, ldb;    // words per row of a0/a1 and of b0/b1
-  int64_t m, n;        // rows of A, rows of B
-  int32_t kw0, kw1;
-  uint64_t mask0, mask1;  // valid bits of the last word of each part
+  // Words of a row are staged in two groups of four: group g of chunk c holds
+  // words cs c .. cs c + 3 from a[g] / b[g], of which those below kg[g] exist
+  // (one part: a[1] = a[0] + 4, cs = 8; the two parts of a Pauli row: one
+  // group each, cs = 4).
+  const uint64_t* a[2];
+  const uint64_t* b[2];
+  int64_t lda, ldb;       // words per row
+  int64_t m, n;           // rows of A, rows of B
+  int32_t kg[2], cs, nch;  // words per group, words per chunk step, chunks
+  uint64_t last;          // valid bits of the row's (or part's) last word
+  int32_t last_w[2];      // that word in each group's count (-1: not in the group)
   uint64_t* C;
   int64_t ldc;
-  int64_t cw;          // words of C written per row: ceil(n / 64)
-  int32_t tm, tn;      // tiles along m and n
-  int32_t sym;         // symmetric table: tiles ti <= tj, mirror written too
+  int64_t cw;             // words of C written per row: ceil(n / 64)
+  int32_t tm, tn;         // tiles along m and n
+  int32_t sym;            // symmetric table: tiles on and above the diagonal, mirror written too
+  int32_t bh;             // rows of tiles per band of the tile order
   int64_t n_tiles;
-  int64_t per_xcd;     // tiles per XCD run
+  int64_t per_xcd;        // tiles per XCD run
 };
-
-// Word w of row r of a two-part operand (p0: kw0 words, then p1: kw1 words),
-// with the last word of each part masked to its valid bits; 0 beyond the
-// rows or the words.  Branch-free: w is the same in every lane, so the part,
-// the offset and the mask are scalar; the row is clamped to a valid address
-// and the lane's result selected.  (Branches here made the compiler wait
-// for each load before issuing the next.)
-__device__ __forceinline__ uint64_t row_word(const uint64_t* p0, const uint64_t* p1, int64_t ld, int64_t r,
-                                             int64_t nrows, int w, int kw0, int kw1, uint64_t m0,
-                                             uint64_t m1) {
-  const bool first = w < kw0;
-  const bool in_k = w < kw0 + kw1;
-  const uint64_t* p = (first || !in_k) ? p0 : p1;
-  const int ww = first ? w : (in_k ? w - kw0 : 0);
-  uint64_t m = !in_k ? 0 : first ? (w == kw0 - 1 ? m0 : ~0ull) : (ww == kw1 - 1 ? m1 : ~0ull);
-  const int64_t rr = r < nrows ? r : nrows - 1;
-  const uint64_t v = p[rr * ld + ww];
-  return r < nrows ? v & m : 0;
-}
-
-__device__ __forceinline__ v8i unpack_fp4(uint32_t d) {
-  v8i o;
-  o[0] = (int)(d & 0x11111111u);
-  o[1] = (int)((d >> 1) & 0x11111111u);
-  o[2] = (int)((d >> 2) & 0x11111111u);
-  o[3] = (int)((d >> 3) & 0x11111111u);
-  o[4] = 0;
-  o[5] = 0;
-  o[6] = 0;
-  o[7] = 0;
-  return o;
-}
 
 // Accumulators start at 2^23: a count below 2^23 added to it stays an exact
 // fp32 integer in [2^23, 2^24), where one unit is the last mantissa bit, so
 // bit 0 of the float's bits is the count's parity.
 constexpr float ACC_BASE = 8388608.0f;
 
-// s_waitcnt operand that waits for LDS (lgkmcnt 0) and nothing else
-// (vmcnt and expcnt at their maximum).
-constexpr int WAIT_LDS = 0xC07F;
+// Bit plane T (bits 4 r + T) of four dwords as an FP4 operand: planes 0, 1, 2
+// are 0.5, 1, 2 as they stand (one AND a dword); plane 3 would be the sign
+// bit and is shifted onto plane 2.  plane_scale: the E8M0 block scale that
+// makes the set value 1.  Which bit meets which k does not matter as long as
+// both operands agree.
+template <int T>
+__device__ __forceinline__ v8i plane_fp4(const uint4& d) {
+  const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+  v8i o;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) o[q] = (int)(T < 3 ? w[q] & (0x11111111u << (T & 3)) : (w[q] >> 1) & 0x44444444u);
+  o[4] = o[5] = o[6] = o[7] = 0;
+  return o;
+}
+constexpr int plane_scale(int t) { return t == 0 ? 128 : (t == 1 ? 127 : 126); }
 
-// Parity bits of the 16 accumulator registers of each 32 x 32 block, as
-// one 16-bit mask per block (bit r = register r).
-template <int WI>
-__device__ __forceinline__ void parity_masks(const v16f (&acc)[WI][4], uint32_t (&par)[WI][4]) {
+// Parities of the 16 accumulators of a 32 x 32 block: this lane half's bits
+// (register 4 q + s at bit 8 q + s + 4).  One funnel shift per accumulator
+// brings its bit 0 in at the top.
+__device__ __forceinline__ uint32_t parity_bits(const v16f& acc) {
+  uint32_t d = 0;
 #pragma unroll
-  for (int i = 0; i < WI; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t m = 0;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) m |= (__float_as_uint(acc[i][j][r]) & 1u) << r;
-      par[i][j] = m;
-    }
+  for (int r = 0; r < 16; ++r) {
+    if (r > 0 && (r & 3) == 0) d >>= 4;
+    d = __builtin_amdgcn_alignbit(__float_as_uint(acc[r]), d, 1);
+  }
+  return d;
 }
 
-// Parities out of a wave's 32 WI x 128 part of the 256 x 256 tile (waves
-// laid out two across: rows (wv >> 1) 32 WI, columns (wv & 1) 128).
-// Register r of block (i, j) in lane (h, l32) is row 32 i + 8 (r / 4) +
-// 4 h + (r % 4), column 32 j + l32 of the part.  scratch: 32 WI x 4 dwords
-// of LDS per wave.
-template <int WI>
-__device__ __forceinline__ void write_tile(const MmArgs& a, const uint32_t (&par)[WI][4], int ti, int tj,
-                                           LDS uint32_t* scratch) {
-  constexpr int PR = 32 * WI;  // rows of the part
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wr = (wv >> 1) * PR, wc = (wv & 1) * 128;
-  const int h = lane >> 5, l32 = lane & 31;
-  const int64_t m0 = (int64_t)ti * MM_T, n0 = (int64_t)tj * MM_T;
-  LDS uint32_t* rows = scratch + wv * (PR * 4);  // [PR rows][4 dwords]
+// a.lanes 32..63 <-> b.lanes 0..31
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+
+// Transposes of two 32 x 32 bit matrices per lane half at once (lane = row,
+// bit = column): five butterfly steps; the 16-lane step swaps register halves
+// between the two, the others fetch the partner lane's word by DPP and merge
+// under the lane's mask.
+__device__ __forceinline__ void transpose32x2(uint32_t& a, uint32_t& b) {
+  const int lane = threadIdx.x & 63;
+  {  // 16: (a.lo, b.lo) and (a.hi, b.hi), odd rows of one against even rows of the other
+    const uint32_t p = __builtin_amdgcn_perm(b, a, 0x05040100u), q = __builtin_amdgcn_perm(b, a, 0x07060302u);
+    const auto r = __builtin_amdgcn_permlane16_swap(p, q, false, false);
+    a = __builtin_amdgcn_perm(r[1], r[0], 0x05040100u);
+    b = __builtin_amdgcn_perm(r[1], r[0], 0x07060302u);
+  }
+  const uint32_t sel8 = (lane & 8) ? 0x03070105u : 0x06020400u;
+  const uint32_t m4 = (lane & 4) ? 0xF0F0F0F0u : 0x0F0F0F0Fu, r4 = (lane & 4) ? 4u : 28u;
+  const uint32_t m2 = (lane & 2) ? 0xCCCCCCCCu : 0x33333333u, r2 = (lane & 2) ? 2u : 30u;
+  const uint32_t m1 = (lane & 1) ? 0xAAAAAAAAu : 0x55555555u, r1 = (lane & 1) ? 1u : 31u;
 #pragma unroll
-  for (int i = 0; i < WI; ++i)
+  for (int k = 0; k < 2; ++k) {
+    uint32_t x = k ? b : a, y;
+    y = dpp<0x128>(x);                               // lane ^ 8
+    x = __builtin_amdgcn_perm(y, x, sel8);
+    y = dpp<0x1B>(dpp<0x141>(x));                    // lane ^ 4: within 8 reversed, then within 4
+    x = (x & m4) | (__builtin_amdgcn_alignbit(y, y, r4) & ~m4);
+    y = dpp<0x4E>(x);                                // lane ^ 2
+    x = (x & m2) | (__builtin_amdgcn_alignbit(y, y, r2) & ~m2);
+    y = dpp<0xB1>(x);                                // lane ^ 1
+    x = (x & m1) | (__builtin_amdgcn_alignbit(y, y, r1) & ~m1);
+    (k ? b : a) = x;
+  }
+}
+
+// Tile order.  Bands of a.bh rows of tiles, each walked column by column, so
+// that the tiles in flight on an XCD (32 workgroups: 4 rows by 8 columns) read
+// few different rows of A and B (65536-string table: 1.72 -> 1.67 ms).  Band b
+// of the symmetric table starts at its first row's diagonal; the few tiles of
+// a band below the diagonal are computed like any other (without a mirror),
+// which costs 1 % of the work at 256 rows of tiles.
+struct TileOrder {
+  int64_t b, r;  // band, place within it
+
+  static __device__ __forceinline__ int64_t first_col(const MmArgs& a, int64_t b) { return a.sym ? b * a.bh : 0; }
+  static __device__ __forceinline__ int64_t height(const MmArgs& a, int64_t b) {
+    const int64_t left = a.tm - b * a.bh;
+    return left < a.bh ? left : a.bh;
+  }
+  // tiles of the bands before b (all of them full)
+  static __device__ __forceinline__ int64_t start(const MmArgs& a, int64_t b) {
+    return a.bh * (b * a.tn - (a.sym ? a.bh * (b * (b - 1) / 2) : 0));
+  }
+  __device__ __forceinline__ void seek(const MmArgs& a, int64_t t) {
+    int64_t lo = 0, hi = (a.tm + a.bh - 1) / a.bh - 1;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi + 1) >> 1;
+      if (start(a, mid) <= t) lo = mid;
+      else hi = mid - 1;
+    }
+    b = lo;
+    r = t - start(a, lo);
+  }
+  // G tiles further.  Past the last tile the band reaches the row count; such
+  // a tile is never multiplied (its loads read the first row).
+  __device__ __forceinline__ void step(const MmArgs& a, int G) {
+    r += G;
+    while (b * a.bh < a.tm) {
+      const int64_t len = height(a, b) * (a.tn - first_col(a, b));
+      if (r < len) break;
+      r -= len;
+      ++b;
+    }
+  }
+  __device__ __forceinline__ void tile(const MmArgs& a, int& ti, int& tj) const {
+    const int h = (int)height(a, b), q = (int)r;
+    if (h <= 0) {
+      ti = a.tm;
+      tj = 0;
+      return;
+    }
+    const int col = h == 4 ? q >> 2 : q / h;
+    ti = (int)(b * a.bh) + q - col * h;
+    tj = (int)first_col(a, b) + col;
+  }
+};
+
+// Parities out of a wave's 64 x 32 BJ part at row r0, column c0.  The
+// instruction's first operand holds B's rows, so a lane holds one row of C
+// and its registers are columns: the row words are packed within the lane.
+template <int BJ>
+__device__ __forceinline__ void write_part(const MmArgs& a, const v16f (&acc)[2][BJ], int64_t r0, int64_t c0,
+                                           bool mirror) {
+  const int lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
+  uint32_t d[BJ];  // row r0 + lane, columns c0 + 32 j ..
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < BJ; ++j) {
+    uint32_t x = parity_bits(acc[0][j]), y = parity_bits(acc[1][j]);
+    swap32(x, y);  // x: lane half 0 of rows 0..31, then of rows 32..63; y: lane half 1
+    d[j] = (x >> 4) | y;
+  }
+  const int64_t gi = r0 + lane;
+  if (gi < a.m) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint64_t bal = __ballot((par[i][j] >> r) & 1u);
-        const int row = 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (l32 == 0) rows[row * 4 + j] = (uint32_t)(bal >> (32 * h));
+    for (int j = 0; j < BJ; j += 2) {
+      const int64_t wcol = c0 / 64 + j / 2;
+      if (wcol < a.cw) {
+        // columns at or beyond n hold the parities of rows that do not exist
+        const int64_t left = a.n - wcol * 64;
+        const uint64_t v = (uint64_t)d[j] | ((uint64_t)d[j + 1] << 32);
+        a.C[gi * a.ldc + wcol] = left >= 64 ? v : v & ((1ull << left) - 1);
       }
-      // one block's ballots at a time (hoisting all of them runs out of registers)
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  __builtin_amdgcn_s_waitcnt(WAIT_LDS);  // LDS only: the next chunks' loads stay in flight
-  __builtin_amdgcn_wave_barrier();
-  // row words: lane -> rows lane (+ 64 p) of the part, two words each
-  const int64_t cword = (n0 + wc) / 64;
-#pragma unroll
-  for (int p = 0; p < PR / 64; ++p) {
-    const int row = lane + 64 * p;
-    const int64_t gi = m0 + wr + row;
-    if (gi < a.m) {
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int64_t wcol = cword + q;
-        if (wcol < a.cw) {
-          const uint64_t v = (uint64_t)rows[row * 4 + 2 * q] | ((uint64_t)rows[row * 4 + 2 * q + 1] << 32);
-          a.C[gi * a.ldc + wcol] = v;
-        }
-      }
     }
   }
-  __builtin_amdgcn_wave_barrier();
-  if (!a.sym || ti == tj) return;
-  // mirrored tile: row (column 32 j + l32 of the part), words over the
-  // part's rows; this lane holds rows 32 i + 8 q + 4 h + s (r = 4 q + s),
-  // so block (i, j)'s mask spreads to bits 8 q + s of a 32-bit word, shifted
-  // by 4 h, and the two lane halves OR together; lane half h writes word h
-  // of the part's PR / 64 words
-  const int64_t rword = (m0 + wr) / 64;
+  if (!mirror) return;
+  // row c0 + 32 (j + h) + l32, the word of rows r0 .. r0 + 63
+  const int64_t wcol = r0 / 64;
+  const int64_t left = a.m - r0;  // may be <= 0: rows beyond the table
+  const uint64_t keep = left >= 64 ? ~0ull : (left <= 0 ? 0ull : (1ull << left) - 1);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    uint32_t d[WI];
-#pragma unroll
-    for (int i = 0; i < WI; ++i) {
-      const uint32_t x = par[i][j];
-      d[i] = ((x & 0xFu) | ((x & 0xF0u) << 4) | ((x & 0xF00u) << 8) | ((x & 0xF000u) << 12)) << (4 * h);
-      d[i] |= (uint32_t)__shfl_xor((int)d[i], 32);
-    }
-    uint64_t w;
-    if constexpr (WI == 4)
-      w = h ? ((uint64_t)d[2] | ((uint64_t)d[3] << 32)) : ((uint64_t)d[0] | ((uint64_t)d[1] << 32));
-    else
-      w = (uint64_t)d[0] | ((uint64_t)d[1] << 32);
-    const int64_t gj = n0 + wc + 32 * j + l32;
-    const int64_t wcol = rword + h;
-    if (h < PR / 64 && gj < a.n && wcol < a.cw) a.C[gj * a.ldc + wcol] = w;
-  }
-}
-
-// Upper-triangle tile t -> (ti, tj): row i of the triangle starts at tile
-// i tn - i (i - 1) / 2; i from the quadratic formula, then corrected by one
-// step either way against rounding.
-__device__ __forceinline__ int64_t tri_start(int64_t i, int64_t tn) { return i * tn - i * (i - 1) / 2; }
-
-__device__ __forceinline__ void tile_coords(const MmArgs& a, int64_t t, int& ti, int& tj) {
-  if (!a.sym) {
-    ti = (int)(t / a.tn);
-    tj = (int)(t % a.tn);
-    return;
-  }
-  const int64_t tn = a.tn;
-  const double b = 2.0 * (double)tn + 1.0;
-  int64_t i = (int64_t)((b - sqrt(b * b - 8.0 * (double)t)) * 0.5);
-  if (i < 0) i = 0;
-  if (i > tn - 1) i = tn - 1;
-  while (i > 0 && tri_start(i, tn) > t) --i;
-  while (i + 1 < tn && tri_start(i + 1, tn) <= t) ++i;
-  ti = (int)i;
-  tj = (int)(i + (t - tri_start(i, tn)));
-}
-
-// The tile G places further in the order (row by row; in the upper
-// triangle row i starts at column i).  Past the last tile ti reaches the
-// row count; such a tile is never multiplied (its loads read clamped rows).
-__device__ __forceinline__ void tile_step(const MmArgs& a, int& ti, int& tj, int G) {
-  tj += G;
-  if (a.sym) {
-    while (tj >= a.tn && ti < a.tn) {
-      ++ti;
-      tj = tj - a.tn + ti;
-    }
-  } else {
-    while (tj >= a.tn) {
-      tj -= a.tn;
-      ++ti;
-    }
+  for (int j = 0; j < BJ; j += 2) {
+    uint32_t x = d[j], y = d[j + 1];
+    transpose32x2(x, y);
+    swap32(x, y);
+    const int64_t gj = c0 + 32 * (j + h) + l32;
+    if (gj < a.n && wcol < a.cw) a.C[gj * a.ldc + wcol] = ((uint64_t)x | ((uint64_t)y << 32)) & keep;
   }
 }
 
@@ -251,291 +245,148 @@ __device__ __forceinline__ void tile_step(const MmArgs& a, int& ti, int& tj, int
 // x * per_xcd + k + j G (j = 0, 1, ...; G workgroups per XCD) of its XCD's
 // run, so the tiles in flight on one XCD are a contiguous window of the
 // tile order and share rows in its L2.  The chunks of all its tiles form one
-// sequence s = j nch + c: chunk s + 1 waits in registers while chunk s is
-// multiplied, goes to the other LDS buffer, and the loads of chunk s + 2
-// start, so the next tile's first chunk is in flight during a tile's parity
-// write-out (which has LDS of its own).
-template <int NW>
-__global__ __launch_bounds__(64 * NW, 1) void gf2mm_kernel(MmArgs a) {
-  constexpr int BS = 64 * NW;    // threads
-  constexpr int WI = 16 / NW;    // 32-row blocks per wave (4 x 4 or 2 x 4 blocks)
-  constexpr int RPT = 2 * MM_T / BS;  // staged rows per thread per chunk
-  // two chunk buffers: [buf][row 0..255 A, 256..511 B][4 words]
-  __shared__ __attribute__((aligned(16))) uint64_t sbuf[2][2 * MM_T][MM_CW];
-  __shared__ __attribute__((aligned(16))) uint32_t wscr[NW * 32 * WI * 4];  // write-out rows, per wave
+// sequence: the next chunk waits in registers while a chunk is multiplied,
+// goes to the other LDS buffer, and the loads of the one after start, so the
+// next tile's first chunk is in flight during a tile's parity write-out.
+//
+// WR x WC wavefronts, each a 64 x 32 BJ part.  Eight lanes load one row's
+// chunk (64 bytes), so a load instruction touches 8 rows; the chunk sits in
+// LDS as two groups of 256 bits a row, and a fragment (32 rows, this lane
+// half's 128 bits of the group) is one conflict-free 16-byte read for four
+// products.
+template <int WR, int WC, int BJ>
+__global__ __launch_bounds__(64 * WR * WC, 2) void gf2mm_kernel(MmArgs a) {
+  constexpr int BS = 64 * WR * WC;
+  constexpr int TI = 64 * WR, TJ = 32 * BJ * WC;  // tile rows, columns
+  constexpr int RS = BS / MM_W;                   // rows per load instruction of the workgroup
+  constexpr int NL = (TI + TJ) / RS;              // loads per thread and chunk
+  static_assert(TI % RS == 0 && TJ % RS == 0, "a load is all A or all B");
+  __shared__ __attribute__((aligned(16))) uint64_t sbuf[2][2][TI + TJ][4];  // [buffer][group][row][word]
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int G = (int)(gridDim.x >> 3);
   const int64_t t_first = (int64_t)(blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
   int64_t t_last = (int64_t)((blockIdx.x & 7) + 1) * a.per_xcd;
   if (t_last > a.n_tiles) t_last = a.n_tiles;
   if (t_first >= t_last) return;
-  const int kw = a.kw0 + a.kw1;
-  const int nch = (kw + MM_CW - 1) / MM_CW;
-  const int64_t n_seq = (t_last - t_first + G - 1) / G * nch;
+  const int nch = a.nch;
+  const int n_my = (int)((t_last - t_first + G - 1) / G);
 
-  // The loads of chunk q are straight-line code (no branch may separate them
+  // The loads of a chunk are straight-line code (no branch may separate them
   // from the stash that uses them, or the compiler waits for each at once):
-  // the tile of q is one of the next three, whose first rows are kept in
-  // rm[0..2] / rn[0..2] (chunk q of a tile past the end loads clamped rows
-  // and is never used); tiles advance by tile_step, without divisions.
+  // its tile is one of the next three, whose first rows are kept in
+  // rm[0..2] / rn[0..2].
   int64_t rm[3], rn[3];
-  int sti, stj;  // tile j + 2
-  tile_coords(a, t_first, sti, stj);
-  rm[0] = (int64_t)sti * MM_T;
-  rn[0] = (int64_t)stj * MM_T;
-  tile_step(a, sti, stj, G);
-  rm[1] = (int64_t)sti * MM_T;
-  rn[1] = (int64_t)stj * MM_T;
-  tile_step(a, sti, stj, G);
-  rm[2] = (int64_t)sti * MM_T;
-  rn[2] = (int64_t)stj * MM_T;
-  // staged row q (0 .. 511: A rows, then B rows) of thread tid: q = tid + BS k
-  uint64_t rr[RPT][MM_CW];
-#define GF2MM_FETCH(JOFF, C)                                                                                    \
-  do {                                                                                                          \
-    const int64_t fm_ = (JOFF) == 0 ? rm[0] : ((JOFF) == 1 ? rm[1] : rm[2]);                                     \
-    const int64_t fn_ = (JOFF) == 0 ? rn[0] : ((JOFF) == 1 ? rn[1] : rn[2]);                                     \
-    _Pragma("unroll") for (int k = 0; k < RPT; ++k) {                                                           \
-      const int q_ = tid + BS * k;                                                                              \
-      const bool isb_ = q_ >= MM_T; /* the same in the whole wave */                                            \
-      const uint64_t* o0_ = isb_ ? a.b0 : a.a0;                                                                 \
-      const uint64_t* o1_ = isb_ ? a.b1 : a.a1;                                                                 \
-      const int64_t ld_ = isb_ ? a.ldb : a.lda;                                                                 \
-      const int64_t r_ = isb_ ? fn_ + q_ - MM_T : fm_ + q_;                                                     \
-      const int64_t nr_ = isb_ ? a.n : a.m;                                                                     \
-      _Pragma("unroll") for (int w = 0; w < MM_CW; ++w) rr[k][w] =                                              \
-          row_word(o0_, o1_, ld_, r_, nr_, (C) * MM_CW + w, a.kw0, a.kw1, a.mask0, a.mask1);                    \
-    }                                                                                                           \
-  } while (0)
-#define GF2MM_STASH(BUF)                                                              \
-  do {                                                                                \
-    _Pragma("unroll") for (int k = 0; k < RPT; ++k)                                   \
-        _Pragma("unroll") for (int w = 0; w < MM_CW; ++w) sbuf[(BUF)][tid + BS * k][w] = rr[k][w]; \
-  } while (0)
-
-  const int wr = (wv >> 1) * (32 * WI), wc = (wv & 1) * 128;  // this wave's part
-  const int h = lane >> 5, l32 = lane & 31;
-  GF2MM_FETCH(0, 0);
-  GF2MM_STASH(0);
-  GF2MM_FETCH(nch > 1 ? 0 : 1, nch > 1 ? 1 : 0);
-  __syncthreads();
-  const int64_t n_my = n_seq / nch;
-  for (int64_t j = 0; j < n_my; ++j) {
-    if (j > 0) {
-      rm[0] = rm[1];
-      rn[0] = rn[1];
-      rm[1] = rm[2];
-      rn[1] = rn[2];
-      tile_step(a, sti, stj, G);
-      rm[2] = (int64_t)sti * MM_T;
-      rn[2] = (int64_t)stj * MM_T;
-    }
-    const int ti = (int)(rm[0] / MM_T), tj = (int)(rn[0] / MM_T);
-    v16f acc[WI][4];
+  TileOrder order;
+  order.seek(a, t_first);
+  auto next_tile = [&](int64_t& r0, int64_t& c0) {
+    int ti, tj;
+    order.tile(a, ti, tj);
+    r0 = (int64_t)ti * TI;
+    c0 = (int64_t)tj * TJ;
+    order.step(a, G);
+  };
 #pragma unroll
-    for (int i = 0; i < WI; ++i)
+  for (int q = 0; q < 3; ++q) next_tile(rm[q], rn[q]);
+  const int lw = tid & (MM_W - 1), lr = tid / MM_W;  // this thread's word of a chunk, and its first row
+  const int lg = lw >> 2, l4 = lw & 3;               // its group, and word of the group
+  const uint64_t* const pa = (lg ? a.a[1] : a.a[0]) + (int64_t)lr * a.lda;
+  const uint64_t* const pb = (lg ? a.b[1] : a.b[0]) + (int64_t)lr * a.ldb;
+  const int kg = lg ? a.kg[1] : a.kg[0], last_w = lg ? a.last_w[1] : a.last_w[0];
+  uint64_t rr[NL], mask = 0;
+  // Words of chunk c of the rows of the tile at (r0, c0).  Only A's words are
+  // masked (bits at or beyond the row length, words past the last; by the
+  // stash, so that nothing here waits for a load): a zero on one side makes
+  // the product zero.  Rows and words that do not exist read
+  // the first row or word; the parities of such rows are not written.
+  auto fetch = [&](int64_t r0, int64_t c0, int c) {
+    const int w = c * a.cs + l4;
+    const bool in_k = w < kg;
+    mask = !in_k ? 0 : (w == last_w ? a.last : ~0ull);
+    const int ww = in_k ? w : 0;
+    const uint64_t* qa = pa + ww;
+    const uint64_t* qb = pb + ww;
+    if (r0 + TI <= a.m && c0 + TJ <= a.n) {  // the same for the workgroup
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][jj][r] = ACC_BASE;
-    for (int c = 0; c < nch; ++c) {
-      const int64_t s = j * nch + c;
-      const int buf = (int)(s & 1);
-      // this lane's fragments: dword 4h + st of each row's chunk at step st,
-      // read just before that step's products
-      const uint32_t* pa0 = (const uint32_t*)&sbuf[buf][wr + l32][2 * h];
-      const uint32_t* pb0 = (const uint32_t*)&sbuf[buf][MM_T + wc + l32][2 * h];
-#pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        v8i oa[WI], ob[4];
-#pragma unroll
-        for (int i = 0; i < WI; ++i) oa[i] = unpack_fp4(pa0[32 * i * 2 * MM_CW + st]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ob[i] = unpack_fp4(pb0[32 * i * 2 * MM_CW + st]);
-#pragma unroll
-        for (int i = 0; i < WI; ++i)
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj)
-            acc[i][jj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(oa[i], ob[jj], acc[i][jj], 4, 4, 0,
-                                                                          SCALE_ONE, 0, SCALE_ONE);
+      for (int k = 0; k < NL; ++k) {
+        const bool isb = k * RS >= TI;
+        const int64_t off = isb ? (c0 + k * RS - TI) * a.ldb : (r0 + k * RS) * a.lda;
+        rr[k] = (isb ? qb : qa)[off];
       }
-      // chunk s + 1 into the other buffer (past the end: a buffer no one
-      // reads), then the loads of chunk s + 2
-      GF2MM_STASH(buf ^ 1);
-      const int c2 = c + 2;
-      const int joff = c2 < nch ? 0 : (c2 < 2 * nch ? 1 : 2);
-      GF2MM_FETCH(joff, c2 - joff * nch);
-      if (c + 1 < nch) __syncthreads();
-    }
-    uint32_t par[WI][4];
-    parity_masks<WI>(acc, par);
-    write_tile<WI>(a, par, ti, tj, (LDS uint32_t*)wscr);
-    __syncthreads();
-  }
-#undef GF2MM_FETCH
-#undef GF2MM_STASH
-}
-
-constexpr int MM_KMAX = 32;  // words of K (per row) the 128 x 128 kernel stages whole
-
-// Whole-K kernel of 128 x 128 tiles (four waves of 64 x 64, 2 x 2 blocks):
-// 67.5 KiB of LDS at K = 32 words, so two workgroups share a CU and one's
-// row staging and parity write-out overlap the other's products.  Bits are
-// unpacked by bit plane: plane t of four consecutive dwords (bits 4r + t)
-// is an operand as it stands, d & (0x11111111 << t), whose FP4 nibbles are
-// 0.5, 1, 2 for t = 0, 1, 2 (block scales 2^1, 2^0, 2^-1); plane 3 would be
-// the sign bit, so it is shifted down to plane 2.  Which bit meets which k
-// does not matter as long as A and B agree.
-constexpr int M2_T = 128;
-constexpr int M2_BS = 256;
-
-__device__ __forceinline__ void write_tile2(const MmArgs& a, v16f (&acc)[2][2], int ti, int tj,
-                                            LDS uint32_t* scratch) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wr = (wv >> 1) * 64, wc = (wv & 1) * 64;
-  const int h = lane >> 5, l32 = lane & 31;
-  const int64_t m0 = (int64_t)ti * M2_T, n0 = (int64_t)tj * M2_T;
-  uint32_t par[2][2];  // bit r: parity of accumulator r of block (i, j)
+    } else {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      uint32_t m = 0;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) m |= ((uint32_t)acc[i][j][r] & 1u) << r;
-      par[i][j] = m;
-    }
-  // row words: ballots over the lanes (columns), one 64-column word per row
-  LDS uint32_t* rows = scratch + wv * (64 * 2);  // [64 rows][2 dwords]
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint64_t bal = __ballot((par[i][j] >> r) & 1u);
-        const int row = 32 * i + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (l32 == 0) rows[row * 2 + j] = (uint32_t)(bal >> (32 * h));
+      for (int k = 0; k < NL; ++k) {
+        const bool isb = k * RS >= TI;
+        const int64_t row = isb ? c0 + k * RS - TI : r0 + k * RS;
+        const bool ok = row + lr < (isb ? a.n : a.m);
+        const int64_t off = row * (isb ? a.ldb : a.lda), first = -(int64_t)lr * (isb ? a.ldb : a.lda);
+        rr[k] = (isb ? qb : qa)[ok ? off : first];
       }
-  __builtin_amdgcn_s_waitcnt(0);
-  __builtin_amdgcn_wave_barrier();
+    }
+  };
+  auto stash = [&](int buf) {
+#pragma unroll
+    for (int k = 0; k < NL; ++k) sbuf[buf][lg][k * RS + lr][l4] = k * RS >= TI ? rr[k] : rr[k] & mask;
+  };
+
+  const int wr = (wv / WC) * 64, wc = (wv % WC) * 32 * BJ;  // this wave's part
+  const int h = lane >> 5, l32 = lane & 31;
+  v16f base;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) base[r] = ACC_BASE;
+  fetch(rm[0], rn[0], 0);
+  stash(0);
   {
-    const int64_t gi = m0 + wr + lane;
-    const int64_t wcol = (n0 + wc) / 64;
-    if (gi < a.m && wcol < a.cw)
-      a.C[gi * a.ldc + wcol] = (uint64_t)rows[lane * 2] | ((uint64_t)rows[lane * 2 + 1] << 32);
-  }
-  if (!a.sym || ti == tj) return;
-  // mirrored tile: the row of column 32 j + l32, one word over the quarter's
-  // 64 rows; this lane holds rows 32 i + 8 q + 4 h + s (r = 4 q + s)
-  const int64_t wcol = (m0 + wr) / 64;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    uint64_t w = 0;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        w |= (uint64_t)((par[i][j] >> r) & 1u) << (32 * i + 8 * (r >> 2) + 4 * h + (r & 3));
-    w |= (uint64_t)__shfl_xor((long long)w, 32);
-    const int64_t gj = n0 + wc + 32 * j + l32;
-    if (h == 0 && gj < a.n && wcol < a.cw) a.C[gj * a.ldc + wcol] = w;
-  }
-}
-
-__global__ __launch_bounds__(M2_BS, 2) void gf2mm_tile2_kernel(MmArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint64_t sm[];  // [2 * M2_T][kwq + 1], kwq = kw rounded to 2
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t t = (int64_t)(blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
-  if (t >= a.n_tiles) return;
-  int ti, tj;
-  tile_coords(a, t, ti, tj);
-  const int64_t m0 = (int64_t)ti * M2_T, n0 = (int64_t)tj * M2_T;
-  const int kw = a.kw0 + a.kw1;
-  const int kwq = (kw + 1) & ~1;  // whole 128-bit groups; the pad word is zero
-  const int ld = kwq + 1;
-  LDS uint64_t* s64 = (LDS uint64_t*)sm;
-  int kwp = 2;
-  while (kwp < kwq) kwp <<= 1;
-  const int per_row = kwp / 2, rows_per = M2_BS / per_row;
-  const int wp = 2 * (tid % per_row), r_first = tid / per_row;
-  for (int r0 = r_first; r0 < 2 * M2_T; r0 += 8 * rows_per) {
-    uint64_t v0[8], v1[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int r = r0 + u * rows_per;
-      v0[u] = v1[u] = 0;
-      if (r < 2 * M2_T && wp < kwq) {
-        if (r < M2_T) {
-          v0[u] = row_word(a.a0, a.a1, a.lda, m0 + r, a.m, wp, a.kw0, a.kw1, a.mask0, a.mask1);
-          v1[u] = row_word(a.a0, a.a1, a.lda, m0 + r, a.m, wp + 1, a.kw0, a.kw1, a.mask0, a.mask1);
-        } else {
-          v0[u] = row_word(a.b0, a.b1, a.ldb, n0 + r - M2_T, a.n, wp, a.kw0, a.kw1, a.mask0, a.mask1);
-          v1[u] = row_word(a.b0, a.b1, a.ldb, n0 + r - M2_T, a.n, wp + 1, a.kw0, a.kw1, a.mask0, a.mask1);
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int r = r0 + u * rows_per;
-      if (r < 2 * M2_T && wp < kwq) {
-        s64[r * ld + wp] = v0[u];
-        s64[r * ld + wp + 1] = v1[u];
-      }
-    }
+    const int q = nch > 1 ? 0 : 1;
+    fetch(q ? rm[1] : rm[0], q ? rn[1] : rn[0], nch > 1 ? 1 : 0);
   }
   __syncthreads();
-
-  v16f acc[2][2];
+  int buf = 0;
+  for (int j = 0; j < n_my; ++j) {
+    v16f acc[2][BJ];
+    for (int c = 0; c < nch; ++c) {
+      // the next chunk into the other buffer (past the end: a buffer no one
+      // reads), then the loads of the one after, in flight during this chunk's
+      // products
+      stash(buf ^ 1);
+      const int c2 = c + 2;
+      const int jo = c2 < nch ? 0 : (c2 < 2 * nch ? 1 : 2);
+      fetch(jo == 0 ? rm[0] : (jo == 1 ? rm[1] : rm[2]), jo == 0 ? rn[0] : (jo == 1 ? rn[1] : rn[2]), c2 - jo * nch);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+      for (int g = 0; g < 2; ++g) {
+        uint4 fa[2], fb[BJ];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+        for (int i = 0; i < 2; ++i) fa[i] = *(const uint4*)&sbuf[buf][g][wr + 32 * i + l32][2 * h];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-  const int wr = (wv >> 1) * 64, wc = (wv & 1) * 64;
-  const int h = lane >> 5, l32 = lane & 31;
-  // a fragment is 128 bits of a row: lane half h takes word pair 2 g + h of
-  // the row's pairs (g = 128-bit group pair), four dwords at once
-  const LDS uint32_t* s32 = (const LDS uint32_t*)sm;
-  const int ld32 = 2 * ld;
-  const LDS uint32_t* pa = s32 + (wr + l32) * ld32 + 4 * h;
-  const LDS uint32_t* pb = s32 + (M2_T + wc + l32) * ld32 + 4 * h;
-  const int ngrp = kwq / 4 + ((kwq % 4) ? 1 : 0);  // 256-bit groups (two 128-bit halves)
-  for (int g = 0; g < ngrp; ++g) {
-    uint32_t da[2][4], db[2][4];
-    const bool half2 = 4 * g + 2 * h < kwq;  // this lane half's words exist
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        da[i][d] = half2 ? pa[32 * i * ld32 + 8 * g + d] : 0u;
-        db[i][d] = half2 ? pb[32 * i * ld32 + 8 * g + d] : 0u;
+        for (int i = 0; i < BJ; ++i) fb[i] = *(const uint4*)&sbuf[buf][g][TI + wc + 32 * i + l32][2 * h];
+#define GF2MM_PLANE(T, C_IN)                                                                                    \
+  do {                                                                                                          \
+    v8i oa[2], ob[BJ];                                                                                          \
+    _Pragma("unroll") for (int i = 0; i < 2; ++i) oa[i] = plane_fp4<T>(fa[i]);                                   \
+    _Pragma("unroll") for (int i = 0; i < BJ; ++i) ob[i] = plane_fp4<T>(fb[i]);                                  \
+    _Pragma("unroll") for (int i = 0; i < 2; ++i) _Pragma("unroll") for (int jj = 0; jj < BJ; ++jj) acc[i][jj] = \
+        __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ob[jj], oa[i], C_IN, 4, 4, 0, plane_scale(T), 0,         \
+                                                        plane_scale(T));                                        \
+  } while (0)
+        if (g == 0 && c == 0)
+          GF2MM_PLANE(0, base);
+        else
+          GF2MM_PLANE(0, acc[i][jj]);
+        GF2MM_PLANE(1, acc[i][jj]);
+        GF2MM_PLANE(2, acc[i][jj]);
+        GF2MM_PLANE(3, acc[i][jj]);
+#undef GF2MM_PLANE
       }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      v8i oa[2], ob[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          oa[i][d] = (int)(t < 3 ? da[i][d] & (0x11111111u << t) : (da[i][d] >> 1) & 0x44444444u);
-          ob[i][d] = (int)(t < 3 ? db[i][d] & (0x11111111u << t) : (db[i][d] >> 1) & 0x44444444u);
-        }
-        oa[i][4] = oa[i][5] = oa[i][6] = oa[i][7] = 0;
-        ob[i][4] = ob[i][5] = ob[i][6] = ob[i][7] = 0;
-      }
-      // nibble value 0.5, 1, 2, 2 for planes 0..3: scales 2^1, 2^0, 2^-1, 2^-1
-      const int sc = t == 0 ? 128 : (t == 1 ? 127 : 126);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(oa[i], ob[j], acc[i][j], 4, 4, 0, sc, 0, sc);
+      __syncthreads();
+      buf ^= 1;
     }
+    write_part<BJ>(a, acc, rm[0] + wr, rn[0] + wc, a.sym && rm[0] < rn[0]);
+    rm[0] = rm[1];
+    rn[0] = rn[1];
+    rm[1] = rm[2];
+    rn[1] = rn[2];
+    next_tile(rm[2], rn[2]);
   }
-  __syncthreads();  // every wave is through with the rows before the epilogue reuses LDS
-  write_tile2(a, acc, ti, tj, (LDS uint32_t*)sm);
 }
 
 // ------------------------------------------------------ phase-pair product --
@@ -729,45 +580,51 @@ __global__ void basis_coeff_kernel(const uint64_t* __restrict__ D, int32_t m, in
   coeff[(int64_t)i * ldc + jw] = w;
 }
 
-zx_status launch_gf2mm(MmArgs a, hipStream_t s) {
-  const int kw = a.kw0 + a.kw1;
-  // General products with K up to 32 words: 128 x 128 tiles, whole K staged
-  // (the parity products: 0.379 -> 0.234 ms for 4096 x 65536 x 1024 bits).
-  // The symmetric table keeps 256 x 256 tiles with K in double-buffered
-  // chunks: with 128 x 128 tiles it took 7.3 ms against 5.3 ms for the
-  // chunked kernel as it then was (four times the tiles, each with its
-  // mirrored write-out).
-  const bool whole = kw <= MM_KMAX && !a.sym;
-  const int T = whole ? M2_T : MM_T;
-  a.tm = (int32_t)((a.m + T - 1) / T);
-  a.tn = (int32_t)((a.n + T - 1) / T);
-  a.n_tiles = a.sym ? (int64_t)a.tn * (a.tn + 1) / 2 : (int64_t)a.tm * a.tn;
+template <int WR, int WC, int BJ>
+zx_status launch_tiles(MmArgs a, int per_cu, hipStream_t s) {
+  constexpr int TI = 64 * WR, TJ = 32 * BJ * WC;
+  a.tm = (int32_t)((a.m + TI - 1) / TI);
+  a.tn = (int32_t)((a.n + TJ - 1) / TJ);
+  static_assert(TI == TJ, "the symmetric table pairs tile (i, j) with (j, i)");
+  a.bh = a.sym && a.tm < 64 ? 1 : 4;  // below, the tiles under the diagonal cost more than the reuse gives
+  a.n_tiles = 0;
+  for (int64_t b = 0; b * a.bh < a.tm; ++b) {
+    const int64_t h = a.tm - b * a.bh < a.bh ? a.tm - b * a.bh : a.bh;
+    a.n_tiles += h * (a.tn - (a.sym ? b * a.bh : 0));
+  }
   a.per_xcd = (a.n_tiles + 7) / 8;
-  const int64_t blocks = 8 * a.per_xcd;
-  if (blocks > 0x7fffffff) {
+  if (a.per_xcd > 0x7fffffff / 8) {
     zx_set_error("product of %lld x %lld rows has too many tiles", (long long)a.m, (long long)a.n);
     return ZX_ECAPACITY;
   }
-  if (whole) {
-    const int kwq = (kw + 1) & ~1;
-    const size_t lds = (size_t)2 * M2_T * (kwq + 1) * 8;
-    static bool attr_set = false;  // the attribute covers the largest staged K
-    if (!attr_set) {
-      ZX_HIP(hipFuncSetAttribute((const void*)gf2mm_tile2_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)((size_t)2 * M2_T * (MM_KMAX + 1) * 8)));
-      attr_set = true;
-    }
-    hipLaunchKernelGGL(gf2mm_tile2_kernel, dim3((unsigned)blocks), dim3(M2_BS), lds, s, a);
-  } else {
-    // one persistent workgroup per CU, the same count on every XCD
-    const ZxDevice* d = zx_device();
-    if (!d) return ZX_EDEVICE;
-    const int64_t per = (d->n_cu / 8) > 0 ? d->n_cu / 8 : 1;
-    const int64_t g = per < a.per_xcd ? per : a.per_xcd;
-    hipLaunchKernelGGL(gf2mm_kernel<MM_NW>, dim3((unsigned)(8 * g)), dim3(64 * MM_NW), 0, s, a);
-  }
+  const ZxDevice* d = zx_device();
+  if (!d) return ZX_EDEVICE;
+  // persistent workgroups, the same count on every XCD
+  const int64_t per = (d->n_cu / 8 > 0 ? d->n_cu / 8 : 1) * per_cu;
+  const int64_t g = per < a.per_xcd ? per : a.per_xcd;
+  hipLaunchKernelGGL((gf2mm_kernel<WR, WC, BJ>), dim3((unsigned)(8 * g)), dim3(64 * WR * WC), 0, s, a);
   ZX_HIP(hipGetLastError());
   return ZX_OK;
+}
+
+// 256 x 256 tiles (one workgroup of eight waves a CU) or 128 x 128 (two of
+// four waves).  The large ones read half the rows per product and are 1.2
+// times as fast where both fill the chip (4096 x 65536 x 1024 bits: 112
+// against 136 us; 65536-string table: 1.67 against 2.1 ms under the profiler); the small ones
+// where the large ones leave CUs without a tile (300 x 5000 x 200 bits: 5.5
+// against 6.7 us) or end on a nearly empty round (8000 strings of 300 qubits,
+// 528 large tiles: 23 against 28 us).
+zx_status launch_gf2mm(const MmArgs& a, hipStream_t s) {
+  const ZxDevice* d = zx_device();
+  if (!d) return ZX_EDEVICE;
+  auto tiles = [&](int64_t e) {
+    const int64_t u = (a.n + e - 1) / e;
+    return a.sym ? u * (u + 1) / 2 : (a.m + e - 1) / e * u;
+  };
+  const int64_t cu = d->n_cu, big = tiles(256);
+  const double t_big = 4.0 * (double)((big + cu - 1) / cu);                              // in 128 x 128 tiles
+  const double t_small = 1.2 * 2.0 * (double)((tiles(128) + 2 * cu - 1) / (2 * cu));
+  return big < cu || t_small < t_big ? launch_tiles<2, 2, 2>(a, 2, s) : launch_tiles<4, 2, 4>(a, 1, s);
 }
 
 }  // namespace
@@ -777,14 +634,17 @@ zx_status zx_pauli_commute_mfma(const uint64_t* X, const uint64_t* Z, int64_t n,
                                 uint64_t* C, int64_t ldc, hipStream_t s) {
   MmArgs a{};
   const int qw = (n_qubits + 63) / 64;
-  a.a0 = X;
-  a.a1 = Z;
-  a.b0 = Z;
-  a.b1 = X;
+  a.a[0] = X;
+  a.a[1] = Z;
+  a.b[0] = Z;
+  a.b[1] = X;
   a.lda = a.ldb = ldq;
   a.m = a.n = n;
-  a.kw0 = a.kw1 = qw;
-  a.mask0 = a.mask1 = (n_qubits % 64) ? ((1ull << (n_qubits % 64)) - 1) : ~0ull;
+  a.kg[0] = a.kg[1] = qw;
+  a.cs = 4;
+  a.nch = (qw + 3) / 4;
+  a.last = (n_qubits % 64) ? ((1ull << (n_qubits % 64)) - 1) : ~0ull;
+  a.last_w[0] = a.last_w[1] = qw - 1;
   a.C = C;
   a.ldc = ldc;
   a.cw = (n + 63) / 64;
@@ -803,16 +663,21 @@ extern "C" zx_status zx_gf2_matmul(const uint64_t* A, int64_t m, int64_t lda, co
   ZX_CHECK_ARG(lda >= kw && ldb >= kw, "lda/ldb below %d words", kw);
   ZX_CHECK_ARG(ldc >= (n + 63) / 64, "ldc below %lld words", (long long)((n + 63) / 64));
   MmArgs a{};
-  a.a0 = A;
-  a.b0 = B;
+  a.a[0] = A;
+  a.a[1] = kw > 4 ? A + 4 : A;
+  a.b[0] = B;
+  a.b[1] = kw > 4 ? B + 4 : B;
   a.lda = lda;
   a.ldb = ldb;
   a.m = m;
   a.n = n;
-  a.kw0 = kw;
-  a.kw1 = 0;
-  a.mask0 = (k_bits % 64) ? ((1ull << (k_bits % 64)) - 1) : ~0ull;
-  a.mask1 = ~0ull;
+  a.kg[0] = kw;
+  a.kg[1] = kw - 4;
+  a.cs = MM_W;
+  a.nch = (kw + MM_W - 1) / MM_W;
+  a.last = (k_bits % 64) ? ((1ull << (k_bits % 64)) - 1) : ~0ull;
+  a.last_w[0] = kw - 1;
+  a.last_w[1] = kw - 5;
   a.C = C;
   a.ldc = ldc;
   a.cw = (n + 63) / 64;

@@ -177,9 +177,6 @@ struct ZxDevice {
 };
 const ZxDevice* zx_device();
 
-// Commutation table on the matrix cores (gf2mm.hip); zx_pauli_commute picks
-// it from this many strings up unless a flag forces a variant.
-constexpr int64_t ZX_PAULI_MFMA_MIN = 1024;
 zx_status zx_pauli_commute_mfma(const uint64_t* X, const uint64_t* Z, int64_t n, int32_t n_qubits, int64_t ldq,
                                 uint64_t* C, int64_t ldc, hipStream_t s);
 

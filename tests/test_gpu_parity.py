@@ -115,3 +115,29 @@ def test_phase_pair_unit_terms(zx, m, n, last):
                                    torch.from_numpy(kb).cuda(), n, phase8, pw)
     torch.cuda.synchronize()
     _compare(mg.cpu().numpy(), eg.cpu().numpy(), mo, eo, 0 if last == "unit" else m)
+
+
+@pytest.mark.parametrize("m,n,k", [(2500, 7000, 700), (1030, 16500, 70), (255, 257, 256), (129, 128, 257),
+                                   (2049, 8200, 520)])
+def test_gf2_matmul_tiles(zx, m, n, k):
+    """Both tile sizes: rows of tiles off the band height of four, ragged
+    rows, columns and words, odd row lengths, junk beyond the last bit."""
+    import torch
+    print("gf2_matmul tiles case", m, n, k, flush=True)
+    rng = np.random.default_rng(m + 3 * n + 5 * k)
+    kw = (k + 63) // 64
+    U = rng.integers(0, 2 ** 64, (m, kw), dtype=np.uint64)
+    F = rng.integers(0, 2 ** 64, (n, kw), dtype=np.uint64)
+    C = zx.gf2_matmul(zx.to_device_words(U), zx.to_device_words(F), k)
+    torch.cuda.synchronize()
+    if k % 64:
+        U[:, -1] &= np.uint64((1 << (k % 64)) - 1)
+        F[:, -1] &= np.uint64((1 << (k % 64)) - 1)
+    rows = sorted({0, 1, 63, 64, 127, 128, m // 2, m - 2, m - 1})
+    Ch = zx.to_host_words(C)
+    for r in (r for r in rows if r < m):
+        assert np.array_equal(Ch[r:r + 1], oracle.gf2_matmul(U[r:r + 1], F, k)), r
+    # every row: the parity of a row of C is that of its A row against the XOR of all B rows
+    tot = np.bitwise_xor.reduce(F, axis=0)
+    want = (np.bitwise_count(U & tot).sum(axis=1) & 1)
+    assert np.array_equal(np.bitwise_count(Ch).sum(axis=1) & 1, want)

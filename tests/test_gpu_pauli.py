@@ -76,3 +76,18 @@ def test_full_size_sampled_rows(zx, variant):
     bits = np.unpackbits(blk.view(np.uint8), axis=1, bitorder="little")[:, :256]
     assert np.array_equal(bits, bits.T)
     assert not bits.diagonal().any()
+
+
+@pytest.mark.parametrize("n,q", [(16500, 130), (16384, 64), (5000, 257), (2049, 1000)])
+def test_tile_orders(zx, n, q):
+    """The matrix-core table in bands of four rows of tiles (from 64 rows of
+    tiles up, the last band short) and row by row, against the vector-unit
+    table."""
+    import torch
+    print("pauli tile order case", n, q, flush=True)
+    X, Z = pauli_strings(300 + q, n, q)
+    dX, dZ = zx.to_device_words(X), zx.to_device_words(Z)
+    C1 = zx.pauli_commute(dX, dZ, q, flags=zx.ZX_PAULI_FORCE_VALU)
+    C2 = zx.pauli_commute(dX, dZ, q, flags=zx.ZX_PAULI_FORCE_MFMA)
+    torch.cuda.synchronize()
+    assert torch.equal(C1, C2)
