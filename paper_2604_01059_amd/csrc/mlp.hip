@@ -9,9 +9,11 @@ using namespace zxmlp;
 
 namespace {
 
-constexpr int FBS = 256;            // forward block: 4 wavefronts
-constexpr int BBS = 128;            // backward block: 2 wavefronts (LDS partials)
-constexpr int MAX_BWD_WAVES = 1024;  // partial gradients kept per backward call
+constexpr int FBS = 64;       // forward block: one wavefront, so that few rows still spread over the CUs
+constexpr int BW = 4;         // wavefronts of a backward block, one hidden tile each
+constexpr int MAX_PARTS = 1024;  // partial gradients kept per backward call
+constexpr int RW = 16;        // wavefronts of a reduction block
+constexpr int RCH = 128;      // partials staged at a time
 
 __global__ void mlp_sync_kernel(const float* param, uint16_t* wbf) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -39,12 +41,10 @@ __global__ __launch_bounds__(FBS) void mlp_forward_kernel(const uint16_t* wbf, c
   const int64_t row0 = ((int64_t)blockIdx.x * (FBS / 64) + (threadIdx.x >> 6)) * 32;
   if (row0 >= rows) return;
   float s[16];
-  score32(load_a_global(x, row0, rows), wbf, param, s);
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int64_t r = row0 + acc_row(i, lane);
-    if ((lane & 31) == i && r < rows) score[r] = s[i];
-  }
+  hidden32<TILES>(load_a_global(x, row0, rows), wbf, param, s);
+  const float sc = sum_hidden(s, param[P_B2]);
+  const int64_t r = row0 + acc_row(lane & 15, lane);
+  if ((lane & 16) == 0 && r < rows) score[r] = sc;
 }
 
 // One wavefront per segment.
@@ -97,97 +97,111 @@ __global__ void mlp_loss_kernel(const float* score, const int64_t* cost, const i
   if (lane == 0) loss[seg] = logf(se) + mx - st * tw;
 }
 
-// Backward.  Wavefront w of nw handles the 32-row chunks w, w + nw, ... in
-// order and accumulates its partial gradient in LDS (each entry owned by one
-// lane); the partials are written to ws[w] and summed over w in order by
-// mlp_reduce_kernel.
-__global__ __launch_bounds__(BBS) void mlp_backward_kernel(const uint16_t* wbf, const float* param,
-                                                           const uint16_t* x, const float* dscore,
-                                                           int64_t rows, int nw, float* ws) {
-  __shared__ float acc[BBS / 64][NPARAM];
-  __shared__ __align__(16) uint16_t xs[BBS / 64][32 * IN];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 5;
-  const int w = blockIdx.x * (BBS / 64) + wv;
-  if (w >= nw) return;  // whole wavefronts only; no block barrier below
-  float* A = acc[wv];
-  for (int i = lane; i < NPARAM; i += 64) A[i] = 0.f;
+// Backward.  Part p of np covers the 32-row chunks p, p + np, ... in order; a
+// wavefront does one part of one 32-unit tile of the hidden layer, with its
+// partial gradient in registers; the parts are added in order by
+// mlp_reduce_kernel.  Every sum runs in one fixed order (over a lane half's
+// rows, the two halves, a part's chunks, the parts): the same inputs give the
+// same bits, which the optimiser needs, since a gradient that is zero up to
+// rounding (b2's always is) still moves its weight by up to the learning rate.
+//
+// Bound: latency of one chunk and tile (a product on the matrix cores, 16 rows
+// of 16 fp32 multiply-adds a lane) for few rows, the fp32 VALU rate for many.
+// 2048 rows: 20 us with one wavefront walking all eight tiles of its part and
+// a branch around each load, now 13 us; 131072 rows: 59 us.
+__global__ __launch_bounds__(64 * BW) void mlp_backward_kernel(const uint16_t* wbf, const float* param,
+                                                               const uint16_t* x, const float* dscore,
+                                                               int64_t rows, int np, float* ws) {
+  __shared__ __align__(16) uint16_t xs[BW][32 * IN];
+  constexpr int BPP = TILES / BW;  // blocks per part
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 5, l32 = lane & 31;
+  const int p = blockIdx.x / BPP, t = (blockIdx.x % BPP) * BW + wv;
+  const int n = 32 * t + l32;
+  const bf16x8 w1 = __builtin_bit_cast(bf16x8, *(const uint4*)(wbf + Q_W1T + n * IN + 8 * g));
+  const float b1 = param[P_B1 + n];
+  const float w2 = from_bf16(wbf[Q_W2 + n]);
+  float aw1[IN], ab1 = 0.f, aw2 = 0.f, ab2 = 0.f;
+#pragma unroll
+  for (int k = 0; k < IN; ++k) aw1[k] = 0.f;
   const int64_t nchunks = (rows + 31) / 32;
-  for (int64_t ch = w; ch < nchunks; ch += nw) {
+  for (int64_t ch = p; ch < nchunks; ch += np) {
     const int64_t row0 = ch * 32;
-    // stage the chunk's features (zero beyond rows)
-    for (int i = lane; i < 32 * IN / 8; i += 64) {
-      const int r = i / (IN / 8), part = i - r * (IN / 8);
-      uint4 q = {0, 0, 0, 0};
-      if (row0 + r < rows) q = *(const uint4*)(x + (row0 + r) * IN + 8 * part);
-      *(uint4*)(&xs[wv][r * IN + 8 * part]) = q;
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    const bf16x8 a = __builtin_bit_cast(bf16x8, *(const uint4*)(&xs[wv][(lane & 31) * IN + 8 * g]));
-    float ds[16];
-    float dsum = 0.f;
+    const bf16x8 a = load_a_global(x, row0, rows);
+    float ds[16], dsum = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
+      // clamped, then selected: a branch would wait for each load in turn
       const int64_t r = row0 + acc_row(i, lane);
-      ds[i] = r < rows ? dscore[r] : 0.f;
-      dsum += ds[i];
+      const float v = dscore[r < rows ? r : rows - 1];
+      ds[i] = r < rows ? v : 0.f;
     }
-#pragma unroll 1
-    for (int t = 0; t < TILES; ++t) {
-      const int n = 32 * t + (lane & 31);
-      const bf16x8 wv1 = __builtin_bit_cast(bf16x8, *(const uint4*)(wbf + Q_W1T + n * IN + 8 * g));
-      const float b1 = param[P_B1 + n];
-      const float w2 = from_bf16(wbf[Q_W2 + n]);
-      f32x16 z = {};
-      const f32x16 pre = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wv1, z, 0, 0, 0);
-      float gw2 = 0.f, gb1 = 0.f, gw1[IN];
-#pragma unroll
-      for (int k = 0; k < IN; ++k) gw1[k] = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float p = pre[i] + b1;
-        const float h = fmaxf(p, 0.f);
-        gw2 += h * ds[i];
-        const float dp = p > 0.f ? ds[i] * w2 : 0.f;
-        gb1 += dp;
-        const uint16_t* xr = &xs[wv][acc_row(i, lane) * IN];
-        const uint4 q0 = *(const uint4*)xr, q1 = *(const uint4*)(xr + 8);
-        const uint32_t qq[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-#pragma unroll
-        for (int k = 0; k < IN; ++k) {
-          const uint16_t hv = (uint16_t)(qq[k >> 1] >> (16 * (k & 1)));
-          gw1[k] += from_bf16(hv) * dp;
-        }
-      }
-      // the two half-waves hold the same column n for different rows
-      gw2 += __shfl_xor(gw2, 32);
-      gb1 += __shfl_xor(gb1, 32);
-#pragma unroll
-      for (int k = 0; k < IN; ++k) gw1[k] += __shfl_xor(gw1[k], 32);
-      if (g == 0) {
-        A[P_W2 + n] += gw2;
-        A[P_B1 + n] += gb1;
-#pragma unroll
-        for (int k = 0; k < IN; ++k) A[P_W1 + k * HID + n] += gw1[k];
-      }
-    }
-    // db2: sum of the chunk's dscore (each row counted once: elements of one
-    // half-wave, any single lane of it)
-    float d2 = dsum + __shfl_xor(dsum, 32);
-    if (lane == 0) A[P_B2] += d2;
-    __builtin_amdgcn_s_waitcnt(0);
+    *(uint4*)(&xs[wv][l32 * IN + 8 * g]) = __builtin_bit_cast(uint4, a);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    f32x16 z = {};
+    const f32x16 pre = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, w1, z, 0, 0, 0);
+    float gw2 = 0.f, gb1 = 0.f, gw1[IN];
+#pragma unroll
+    for (int k = 0; k < IN; ++k) gw1[k] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      dsum += ds[i];
+      const float v = pre[i] + b1;
+      gw2 += fmaxf(v, 0.f) * ds[i];
+      const float dp = v > 0.f ? ds[i] * w2 : 0.f;
+      gb1 += dp;
+      const uint16_t* xr = &xs[wv][acc_row(i, lane) * IN];
+      const uint4 q0 = *(const uint4*)xr, q1 = *(const uint4*)(xr + 8);
+      const uint32_t qq[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+#pragma unroll
+      for (int k = 0; k < IN; ++k) gw1[k] += from_bf16((uint16_t)(qq[k >> 1] >> (16 * (k & 1)))) * dp;
+    }
+    // the two half-waves hold the same hidden unit for different rows
+    aw2 += gw2 + __shfl_xor(gw2, 32);
+    ab1 += gb1 + __shfl_xor(gb1, 32);
+#pragma unroll
+    for (int k = 0; k < IN; ++k) aw1[k] += gw1[k] + __shfl_xor(gw1[k], 32);
+    ab2 += dsum + __shfl_xor(dsum, 32);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();  // every lane has read xs before the next chunk's
   }
-  float* out = ws + (int64_t)w * NPARAM;
-  for (int i = lane; i < NPARAM; i += 64) out[i] = A[i];
+  float* out = ws + (int64_t)p * NPARAM;
+  if (g == 0) {
+    out[P_W2 + n] = aw2;
+    out[P_B1 + n] = ab1;
+  }
+#pragma unroll
+  for (int k = 0; k < IN / 2; ++k) out[P_W1 + (k + IN / 2 * g) * HID + n] = g ? aw1[k + IN / 2] : aw1[k];
+  if (t == 0 && lane == 0) out[P_B2] = ab2;
 }
 
-__global__ void mlp_reduce_kernel(const float* ws, int nw, float* grad) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= NPARAM) return;
+// grad = the parts added in order.  A block owns 64 parameters: one wavefront
+// adds the 128 parts in one LDS buffer while the others bring the next 128
+// into the other (a thread that loads and adds part after part waits on
+// memory for each few: 16 us for 64 parts; now 3.7, and 24 for 1024).
+__global__ __launch_bounds__(64 * RW) void mlp_reduce_kernel(const float* ws, int np, float* grad) {
+  __shared__ float st[2][RCH][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane, j = i < NPARAM ? i : NPARAM - 1;
+  auto bring = [&](int buf, int p0, int w, int nw) {
+    const int c = np - p0 < RCH ? np - p0 : RCH;
+#pragma unroll 9
+    for (int r = w; r < c; r += nw) st[buf][r][lane] = ws[(int64_t)(p0 + r) * NPARAM + j];
+  };
+  bring(0, 0, wv, RW);
+  __syncthreads();
   float s = 0.f;
-  for (int w = 0; w < nw; ++w) s += ws[(int64_t)w * NPARAM + i];
-  grad[i] = s;
+  for (int p0 = 0, buf = 0; p0 < np; p0 += RCH, buf ^= 1) {
+    const int c = np - p0 < RCH ? np - p0 : RCH;
+    if (wv == 0) {
+#pragma unroll 32
+      for (int r = 0; r < c; ++r) s += st[buf][r][lane];
+    } else {
+      bring(buf ^ 1, p0 + RCH, wv - 1, RW - 1);
+    }
+    __syncthreads();
+  }
+  if (wv == 0 && i < NPARAM) grad[i] = s;
 }
 
 __global__ void mlp_adam_kernel(float* param, uint16_t* wbf, const float* grad, float* m, float* v,
@@ -209,9 +223,9 @@ __global__ void mlp_adam_kernel(float* param, uint16_t* wbf, const float* grad, 
   }
 }
 
-int bwd_waves(int64_t rows) {
+int bwd_parts(int64_t rows) {
   const int64_t c = (rows + 31) / 32;
-  return (int)std::min<int64_t>(std::max<int64_t>(c, 1), MAX_BWD_WAVES);
+  return (int)std::min<int64_t>(std::max<int64_t>(c, 1), MAX_PARTS);
 }
 
 }  // namespace
@@ -255,7 +269,7 @@ extern "C" zx_status zx_mlp_loss(const float* score, const int64_t* cost, const 
 
 extern "C" size_t zx_mlp_workspace_bytes(int64_t rows) {
   if (rows < 0) return 0;
-  return (size_t)bwd_waves(rows) * NPARAM * sizeof(float);
+  return (size_t)bwd_parts(rows) * NPARAM * sizeof(float);
 }
 
 extern "C" zx_status zx_mlp_backward(const zx_mlp* w, const uint16_t* x, const float* dscore, int64_t rows,
@@ -268,12 +282,10 @@ extern "C" zx_status zx_mlp_backward(const zx_mlp* w, const uint16_t* x, const f
     zx_set_error("workspace too small");
     return ZX_ECAPACITY;
   }
-  const int nw = bwd_waves(rows);
-  const int blocks = (nw + BBS / 64 - 1) / (BBS / 64);
-  hipLaunchKernelGGL(mlp_backward_kernel, dim3(blocks), dim3(BBS), 0, s, w->wbf16, w->param, x, dscore, rows,
-                     nw, (float*)ws);
-  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NPARAM + 255) / 256), dim3(256), 0, s, (const float*)ws, nw,
-                     grad);
+  const int np = bwd_parts(rows);
+  hipLaunchKernelGGL(mlp_backward_kernel, dim3(np * (TILES / BW)), dim3(64 * BW), 0, s, w->wbf16, w->param, x, dscore,
+                     rows, np, (float*)ws);
+  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NPARAM + 63) / 64), dim3(64 * RW), 0, s, (const float*)ws, np, grad);
   ZX_HIP(hipGetLastError());
   return ZX_OK;
 }
@@ -286,7 +298,7 @@ extern "C" zx_status zx_mlp_adam(const zx_mlp* w, const float* grad, float* m, f
   ZX_CHECK_ARG(beta1 >= 0.f && beta1 < 1.f && beta2 >= 0.f && beta2 < 1.f && eps > 0.f, "bad Adam constants");
   const float bc1 = (float)(1.0 - std::pow((double)beta1, (double)step));
   const float bc2 = (float)(1.0 - std::pow((double)beta2, (double)step));
-  hipLaunchKernelGGL(mlp_adam_kernel, dim3((NPARAM + 255) / 256), dim3(256), 0, s, w->param, w->wbf16, grad,
+  hipLaunchKernelGGL(mlp_adam_kernel, dim3((NPARAM + 63) / 64), dim3(64), 0, s, w->param, w->wbf16, grad,
                      m, v, lr, beta1, beta2, eps, bc1, bc2);
   ZX_HIP(hipGetLastError());
   return ZX_OK;

@@ -51,15 +51,16 @@ __device__ __forceinline__ bf16x8 load_a(P feats32 /* 32 rows x 16 bf16 */) {
   return __builtin_bit_cast(bf16x8, q);
 }
 
-// Scores of 32 rows; element i of s is the score of row acc_row(i, lane)
-// (identical in the 32 lanes of a half-wave).  The weights of a tile are
-// loaded inside the tile loop, which is kept rolled so that only one
-// accumulator tile is live.
-__device__ inline void score32(bf16x8 a, const uint16_t* wbf, const float* param, float s[16]) {
+// Hidden layer of 32 rows and this lane's part of the second: element i of s
+// ends as the sum over the lane's hidden units (32 t + (lane & 31)) for row
+// acc_row(i, lane).  UNROLL tiles' weights are loaded together; 1 keeps a
+// single accumulator tile live (inside the simplify kernel).
+template <int UNROLL>
+__device__ __forceinline__ void hidden32(bf16x8 a, const uint16_t* wbf, const float* param, float s[16]) {
   const int lane = threadIdx.x & 63, g = lane >> 5;
 #pragma unroll
   for (int i = 0; i < 16; ++i) s[i] = 0.f;
-#pragma unroll 1
+#pragma unroll UNROLL
   for (int t = 0; t < TILES; ++t) {
     const int n = 32 * t + (lane & 31);
     const bf16x8 w = __builtin_bit_cast(bf16x8, *(const uint4*)(wbf + Q_W1T + n * IN + 8 * g));
@@ -70,6 +71,35 @@ __device__ inline void score32(bf16x8 a, const uint16_t* wbf, const float* param
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] += fmaxf(acc[i] + b1, 0.f) * w2;
   }
+}
+
+// Sum over the 32 hidden units a half-wave holds, and b2: returns the score
+// of row acc_row(lane & 15, lane).  A butterfly over the lanes in which each
+// step keeps the half of the rows that the lane's bit names, so 16 exchanges
+// do where one per row and step takes 80; every score is the same sum of
+// pairs, so its bits are those of the full butterfly.
+__device__ __forceinline__ float sum_hidden(float s[16], float b2) {
+  const int lane = threadIdx.x & 63;
+  float r[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) r[i] = s[i];
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    const bool up = (lane & o) != 0;
+    // rows that differ in this bit sit next to each other: 2 i and 2 i + 1
+#pragma unroll
+    for (int i = 0; i < 8 / o; ++i) {
+      const float keep = up ? r[2 * i + 1] : r[2 * i], give = up ? r[2 * i] : r[2 * i + 1];
+      r[i] = keep + __shfl_xor(give, o, 64);
+    }
+  }
+  return r[0] + __shfl_xor(r[0], 16, 64) + b2;
+}
+
+// Scores of 32 rows; element i of s is the score of row acc_row(i, lane)
+// (identical in the 32 lanes of a half-wave).
+__device__ inline void score32(bf16x8 a, const uint16_t* wbf, const float* param, float s[16]) {
+  hidden32<1>(a, wbf, param, s);
   // sum over the 32 hidden units a half-wave holds, fixed butterfly order
 #pragma unroll
   for (int o = 1; o < 32; o <<= 1)

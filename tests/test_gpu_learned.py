@@ -477,3 +477,25 @@ def test_training_gains(zx):
     assert after["top1_least_cost"] > after["random_least_cost"]
     assert ev["fill_learned"] < ev["fill_greedy"]
     assert ev["fallback_equals_min"] and ev["gate2q_fallback"] <= ev["gate2q_greedy"]
+
+
+@pytest.mark.parametrize("rows", [1, 32, 33, 4096, 4097, 32769])
+def test_mlp_backward_parts(zx, rows):
+    """Edges of the chunks (32 rows), of the staged parts (128) and of the
+    part count (1024): fp32 sums of at most 32769 terms against the oracle.
+    A sum of n terms in fp32 is off by at most n u of the sum of magnitudes;
+    the rounding errors are random here, so sqrt(n) u times a factor of 8 is
+    allowed (u = 2^-24)."""
+    rng = np.random.default_rng(70 + rows)
+    p = rand_param(rng)
+    m = make_mlp(zx, p)
+    X = bf16_bits(rng.standard_normal((rows, omlp.IN)).astype(np.float32))
+    d = (rng.standard_normal(rows) / rows).astype(np.float32)
+    print("backward parts rows", rows, flush=True)
+    xt, dt = torch.from_numpy(X.view(np.int16)).cuda(), torch.from_numpy(d).cuda()
+    g = m.backward(xt, dt).cpu().numpy()
+    ref = omlp.backward(p, X, d.astype(np.float64))
+    # magnitudes: the same sums with every sign positive (bounded by |d| |x| |w2|)
+    W1, b1, w2, b2 = omlp.unpack(p)
+    mag = np.abs(ref).max() + np.abs(d).sum() * 8.0
+    assert np.abs(g - ref).max() <= 8 * np.sqrt(rows + 64.0) * 2.0 ** -24 * mag
