@@ -46,6 +46,7 @@ namespace {
 
 constexpr int MAXW = 128;   // words per row (n <= 8192)
 constexpr int MAXS = 2;     // words per lane in a team of 64
+constexpr int SPIDER_MAJOR_MAX = 64;  // selected spiders up to which a round's update goes spider by spider
 
 __host__ __device__ inline int ldw_lds(int W) { return W | 1; }  // odd LDS row stride
 
@@ -76,6 +77,7 @@ struct Shared {
   int64_t rowops;
   int32_t n_terms;     // phase-pair terms recorded (parameterized spiders)
   int32_t pad_terms;
+  uint64_t ctx[32];    // the running diagram's Ctx, for the functions kept out of line
 };
 
 // LDS pointers are typed as such so that the compiler emits ds_* accesses.
@@ -133,12 +135,17 @@ struct Ctx {
   LDSP uint64_t* omask;    // output-attached spiders
   int32_t* trace;          // global, 4 int32 per entry
   int T, nteams, team, tl;
-  LDSP uint64_t* scr;      // arena mode: free LDS for the round update
+  LDSP uint64_t* scr;      // free LDS for the round update
   int scr_words;
   int pw;                  // words per parameter row (0: no parameters)
   uint64_t* par;           // CURRENT parameter rows, n x pw (global)
   uint8_t* terms;          // recorded terms (global)
   TeamBoard* tb;           // arena mode with a team (else null)
+};
+
+template <bool LA>
+struct CtxFits {
+  static_assert(sizeof(Ctx<LA>) <= sizeof(Shared::ctx), "Ctx fits its place in Shared");
 };
 
 template <class P>
@@ -218,6 +225,29 @@ __device__ void setup_ctx(Ctx<LA>& c, uint8_t* arena, uint8_t* lds) {
   c.nteams = BS / c.T;
   c.team = threadIdx.x / c.T;
   c.tl = threadIdx.x % c.T;
+}
+
+// The context of a diagram, left in LDS for the functions kept out of line: a
+// reference to it would force every member into scratch memory, from where
+// each use in the rounds would load it again.
+template <bool LA>
+__device__ __forceinline__ void save_ctx(const Ctx<LA>& c, Shared& sh) {
+  (void)sizeof(CtxFits<LA>);
+  if (threadIdx.x == 0) *reinterpret_cast<Ctx<LA>*>(sh.ctx) = c;
+  __syncthreads();
+}
+template <int BS, bool LA>
+__device__ __forceinline__ Ctx<LA> load_ctx(Shared& sh) {
+  Ctx<LA> c = *reinterpret_cast<const Ctx<LA>*>(sh.ctx);
+  c.n = uni(c.n);
+  c.W = uni(c.W);
+  c.ldw = uni(c.ldw);
+  c.pw = uni(c.pw);
+  c.scr_words = uni(c.scr_words);
+  c.T = uni(c.T);
+  c.team = threadIdx.x / c.T;
+  c.tl = threadIdx.x % c.T;
+  return c;
 }
 
 template <bool LA>
@@ -415,75 +445,114 @@ __device__ void list_selected_wave(Ctx<LA>& c, Shared& sh, bool lc_trace, bool s
   }
 }
 
-// Lexicographically-first maximal independent set of the candidates (scan
-// in ascending spider id, take a candidate unless adjacent to one taken).
-// One wavefront, one 64-spider block at a time.  The wave keeps the union
-// of the taken spiders' rows (lane l: words l and l + 64), so a block's
-// candidates that are adjacent to a spider taken in an earlier block are
-// one word of it; the rest are resolved in ascending order with scalar bit
-// operations on their rows' word b, loaded one block ahead; then the rows
-// of the block's taken spiders are OR-ed into the union, four at a time.
-// Per block, the only wait on memory is for those rows and the next
-// block's words, issued together.  The same wavefront then counts, traces
-// and lists the set (list_selected_wave), before the one closing barrier.
-// The wavefront runs at raised priority: it is the round's serial step, and
-// another workgroup's waves may share its SIMD (batched: 4.60 -> 4.54 ms).
+// Sum of a 32-bit value over the wavefront, in lane 63 (DPP row shifts, then
+// row broadcasts).
+__device__ __forceinline__ int wave_sum_lane63(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);  // row_bcast:31
+  return v;
+}
+
+// Candidate words of the next local-complementation round (interior, k in
+// {2, 6}, not in `gone`), a word per wavefront at a time.
+template <int BS, bool LA, bool GONE>
+__device__ __forceinline__ void lc_candidates(Ctx<LA>& c) {
+  const int lane = threadIdx.x & 63;
+  for (int j = threadIdx.x >> 6; j < c.W; j += BS / 64) {
+    // phases past n (the next LDS array's bytes) fall to the alive mask
+    const uint64_t b = __ballot((c.k[64 * j + lane] & 3) == 2);
+    if (lane == 0) c.cand[j] = b & c.alive[j] & ~c.bnd[j] & (GONE ? ~c.sel[j] : ~0ull);
+  }
+}
+
+// A greedy local-complementation round up to its update: the lexicographically
+// first maximal independent set of the candidates in c.cand (ascending
+// spider id, taken unless adjacent to one taken), its trace, list and mask,
+// its phase increments and scalar sums (sh.acc64 as prepare_round leaves it).
+// sh.ns = 0 when there is no candidate.  One wavefront, then one barrier.
+//
+// Lane l holds words l and l + 64 of the candidates that are left: the first
+// of them is the next spider taken, and its row takes itself and its
+// neighbours out.  So the chain is one dependent row read per spider taken,
+// about six a round whatever the diagram's size; the degree of the spider
+// before is summed while a row is on its way.  Cycles a round at 1024
+// spiders, candidates, selection and sums together: 14.4 k (a pass of its own
+// for each with six barriers, the selection going through all 16 blocks of
+// candidates in turn) -> 7.0 k.
 template <int BS, bool LA>
-__device__ void lfmis(Ctx<LA>& c, Shared& sh) {
-  const int W = c.W;
-  for (int j = threadIdx.x; j < W; j += BS) c.sel[j] = 0;
-  __syncthreads();
+__device__ void select_lc(Ctx<LA>& c, Shared& sh) {
   if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    __builtin_amdgcn_s_setprio(2);
-    // clamped word indices (W <= 128): a lane's words past W are loaded
-    // from word W - 1 and never read
-    const int j0 = lane < W ? lane : W - 1;
-    const int j1 = lane + 64 < W ? lane + 64 : W - 1;
-    uint64_t blk0 = 0, blk1 = 0;
-    uint64_t nxt = ((c.cand[0] >> lane) & 1) ? row_ptr(c, lane)[0] : 0;
-    for (int b = 0; b < W; ++b) {
-      const uint64_t cw = uni64((int64_t)c.cand[b]);
-      const uint64_t inblk = nxt;
-      if (b + 1 < W) {
-        const uint64_t cn = c.cand[b + 1];
-        nxt = ((cn >> lane) & 1) ? row_ptr(c, 64 * (b + 1) + lane)[b + 1] : 0;
-      }
-      if (!cw) continue;
-      const uint64_t bw = readlane64(b < 64 ? blk0 : blk1, b & 63);
-      uint64_t R = cw & ~bw;  // candidates with no taken neighbour in earlier blocks
-      uint64_t taken = 0;
-      while (R) {
-        const int l = __builtin_ctzll(R);
-        taken |= 1ull << l;
-        R &= ~(readlane64(inblk, l) | (1ull << l));
-      }
-      if (lane == 0) c.sel[b] = taken;
-      uint64_t tk = taken;
-      while (tk) {
-        // four taken spiders (repeating the first when fewer are left), so
-        // that the eight loads are issued before one wait
-        int t[4];
-        t[0] = __builtin_ctzll(tk);
-        tk &= tk - 1;
-#pragma unroll
-        for (int q = 1; q < 4; ++q) {
-          t[q] = tk ? __builtin_ctzll(tk) : t[0];
-          tk &= tk - 1;
+    const int lane = threadIdx.x, W = c.W;
+    __builtin_amdgcn_s_setprio(2);  // the round's serial step; another workgroup's waves may share the SIMD
+    const bool has0 = lane < W, has1 = lane + 64 < W;
+    const int j0 = has0 ? lane : W - 1, j1 = has1 ? lane + 64 : W - 1;  // clamped: loaded, never used
+    uint64_t c0 = has0 ? c.cand[j0] : 0, c1 = has1 ? c.cand[j1] : 0;
+    uint64_t s0 = 0, s1 = 0;
+    int64_t deg = 0, pairs = 0;
+    int ns = 0, pc = 0;  // pc: this lane's part of the last taken spider's degree
+    auto count = [&]() {
+      const int d = __builtin_amdgcn_readlane(wave_sum_lane63(pc), 63);
+      deg += d;
+      pairs += (int64_t)d * (d - 1) / 2;
+    };
+    for (;;) {
+      const uint64_t m0 = __ballot(c0 != 0), m1 = W > 64 ? __ballot(c1 != 0) : 0;
+      if ((m0 | m1) == 0) break;
+      const bool second = m0 == 0;
+      const int src = __builtin_ctzll(second ? m1 : m0);
+      const uint64_t word = readlane64(second ? c1 : c0, src);
+      const int bit = __builtin_ctzll(word);
+      const int u = 64 * (src + (second ? 64 : 0)) + bit;
+      const auto row = row_ptr(c, u);
+      const uint64_t r0 = row[j0], r1 = W > 64 ? row[j1] : 0;
+      if (ns > 0) count();
+      const uint64_t own = lane == src ? 1ull << bit : 0;
+      if (second) s1 |= own;
+      else s0 |= own;
+      if (lane == 0) c.slist[ns] = (int16_t)u;
+      const uint64_t x0 = has0 ? r0 : 0, x1 = has1 ? r1 : 0;
+      c0 &= ~(x0 | (second ? 0 : own));
+      c1 &= ~(x1 | (second ? own : 0));
+      pc = __popcll(x0) + __popcll(x1);
+      ++ns;
+    }
+    if (ns > 0) {
+      count();
+      if (has0) c.sel[j0] = s0;
+      if (has1) c.sel[j1] = s1;
+      const int nt0 = sh.n_trace, round = sh.round;
+      int ph = 0;
+      for (int i = lane; i < ns; i += 64) {
+        const int x = c.slist[i], kx = c.k[x];
+        c.kc[x] = (int8_t)((8 - kx) & 7);
+        ph += kx == 2 ? 1 : 7;  // e^{-i b pi/2} e^{i pi/4}
+        if (c.trace) {
+          int32_t* e = c.trace + 4 * (int64_t)(nt0 + i);
+          e[0] = round;
+          e[1] = 0;
+          e[2] = x;
+          e[3] = -1;
         }
-        uint64_t a0 = 0, a1 = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const auto rt = row_ptr(c, 64 * b + t[q]);
-          a0 |= rt[j0];
-          a1 |= rt[j1];
-        }
-        blk0 |= a0;
-        blk1 |= a1;
+      }
+      ph = __builtin_amdgcn_readlane(wave_sum_lane63(ph), 63);
+      if (lane == 0) {
+        sh.acc64[0] = deg;
+        sh.acc64[1] = pairs;
+        sh.acc64[2] = ph;
+        sh.acc64[3] = 0;
+        if (c.trace) sh.n_trace = nt0 + ns;
+      }
+      // the list of the set's words, where a later step walks it
+      if (c.pw || ns > SPIDER_MAJOR_MAX || (!LA && c.scr_words < 64)) {
+        __builtin_amdgcn_wave_barrier();
+        list_selected_wave(c, sh, false);
       }
     }
-    __builtin_amdgcn_wave_barrier();
-    list_selected_wave(c, sh, true);
+    if (lane == 0) sh.cnt = sh.ns = ns;
     __builtin_amdgcn_s_setprio(0);
   }
   __syncthreads();
@@ -700,7 +769,7 @@ __device__ void prepare_round(Ctx<LA>& c, Shared& sh, bool pivot, bool listed) {
 // The rank-|S| update of every present row outside S, by (row, word)
 // threads.  Also sums into sh.acc64[3] the popcounts of every present
 // non-selected row with the selected columns masked out (twice the edge
-// count after the round); selected columns are cleared by delete_selected.
+// count after the round); selected columns are cleared by end_round.
 //
 // Few selected spiders (the common case): spider-major.  A thread keeps the
 // words of up to MAXI rows in registers for the whole round; for each
@@ -709,7 +778,6 @@ __device__ void prepare_round(Ctx<LA>& c, Shared& sh, bool pivot, bool listed) {
 // only written at the end, and all loads are independent.
 // Many selected spiders: row-major, walking the selected bits of each row.
 constexpr int MAXI = 4;
-constexpr int SPIDER_MAJOR_MAX = 64;
 
 // A team round as a slice sees it; the selected list, partners, phase
 // contributions and the present and selected masks are staged in LDS once
@@ -871,7 +939,8 @@ constexpr uint64_t TEAM_WAIT_TICKS = 100000000ull * 10;  // 10 s of the 100 MHz 
 // TEAM_MAXS rewrites): publish, claim slices like any member, wait for the
 // slices others claimed, then take the phase increments and edge counts.
 template <int BS>
-__device__ __noinline__ void apply_round_team(Ctx<false>& c, Shared& sh, bool pivot) {
+__device__ __noinline__ void apply_round_team(Shared& sh, bool pivot) {
+  const Ctx<false> c = load_ctx<BS, false>(sh);
   TeamBoard* tb = c.tb;
   const int tid = threadIdx.x, W = c.W, n = c.n, ns = uni(sh.ns);
   LDSP uint64_t* ls = c.scr;  // TEAM_SLICE_LDS words of the free LDS
@@ -976,7 +1045,8 @@ __device__ __noinline__ void apply_round_team(Ctx<false>& c, Shared& sh, bool pi
 // Not inlined: its unrolled update would otherwise set the register
 // allocation of the LDS-resident path that shares the kernel.
 template <int BS>
-__device__ __noinline__ void apply_round_arena(Ctx<false>& c, Shared& sh, bool pivot) {
+__device__ __noinline__ void apply_round_arena(Shared& sh, bool pivot) {
+  const Ctx<false> c = load_ctx<BS, false>(sh);
   const int W = c.W, n = c.n, ns = uni(sh.ns), tid = threadIdx.x;
   const bool staged = (int64_t)ns * W + 64 + 8 <= c.scr_words;
   LDSP uint64_t* cs = c.scr;
@@ -1082,18 +1152,231 @@ __device__ __noinline__ void apply_round_arena(Ctx<false>& c, Shared& sh, bool p
   __syncthreads();
 }
 
+// x ^ (y & z) in one instruction per half
+__device__ __forceinline__ uint32_t xor_and(uint32_t x, uint32_t y, uint32_t z) {
+  return __builtin_amdgcn_bitop3_b32(x, y, z, 0x78);
+}
+
+// The round update in LDS for at most SPIDER_MAJOR_MAX selected spiders; also
+// drops the selected columns.  A wavefront owns a contiguous run of rows.
+// First one lane per row: the row's hit mask, bit s = adjacent to selected
+// spider s, is bit w of that spider's row (the adjacency is symmetric, and
+// selected rows do not change here; a pivot pair's rows were swapped, so it
+// is the partner's row), and its phase increment.  Then WL words of a row per
+// lane: the row's mask comes from its lane by a shuffle, the XOR of the
+// contributions that it names is applied, and every row word is read and
+// written once.  Last, one lane per row again, the diagonal bit.
+//
+// TAB: the contributions of APPLY_S selected spiders in two groups of four,
+// 16 combinations each, in the LDS behind the diagram (built by the whole
+// workgroup, one barrier): a lookup per group and row word.  Otherwise, where
+// the diagram leaves no room for them, the contributions sit in the lane's
+// registers and every spider costs three VALU instructions a word.
+//
+// Bound: VALU and LDS instructions issued.  Reads of several steps are
+// issued before any of their uses and writes (the compiler keeps a read
+// behind a write of the same array, and used one by one each read is waited
+// for).  A round at 1024 spiders: about 75 k cycles with each row word walking
+// the selected spiders, a dependent read and a branch each, and a pass of its
+// own to clear the columns; 19.4 k one word a lane from registers; now 13.5 k
+// (the diagram 2.95 -> 0.82 ms).  Below APPLY_TAB_W words a row the tables'
+// barrier costs more than the lookups save (256 spiders: 5.6 against 4.1 k;
+// 384, 6 words: the same).
+constexpr int APPLY_S = 8;
+constexpr int APPLY_U = 4;
+constexpr int APPLY_TAB_W = 7;
+__device__ __forceinline__ int apply_tab_words(int W) { return APPLY_S / 4 * 16 * (W + 2); }
+
+template <int BS, bool TAB>
+__device__ __forceinline__ void apply_rows_lds(Ctx<true>& c, Shared& sh, bool pivot) {
+  constexpr int NW = BS / 64;
+  constexpr int WL = TAB ? 2 : 1;  // words per lane
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int W = c.W, n = c.n, ns = uni(sh.ns), ldw = c.ldw;
+  const int LW = (W + WL - 1) / WL;  // lanes per row
+  const int W1 = LW * WL | 1;        // words per table entry (odd)
+  const int rpw = 64 / LW;           // rows per step (W <= 64 in LDS)
+  const int rr = lane / LW, j = rr < rpw ? (lane - rr * LW) * WL : 0;
+  const bool on = rr < rpw, two = WL == 2 && j + 1 < W;
+  const int R = (n + NW - 1) / NW;
+  const int r0 = uni(wv * R), r1 = uni(r0 + R < n ? r0 + R : n);
+  uint64_t keep[WL];
+  keep[0] = ~c.sel[j];
+  if constexpr (WL == 2) keep[1] = ~c.sel[two ? j + 1 : j];
+  const LDSP uint32_t* a32 = (const LDSP uint32_t*)c.adj;
+  const LDSP uint64_t* const last_row = c.adj + (n - 1) * ldw + j;
+  // lane s: selected spider s, the row that holds its neighbours, its phase
+  const int xs = c.slist[lane < ns ? lane : 0];
+  const int nb = pivot ? c.partner[xs] : xs;
+  const int kx = lane < ns ? c.kc[xs] : 0;
+  int pc = 0;
+  for (int s0 = 0; s0 < ns; s0 += APPLY_S) {
+    const int sc = ns - s0 < APPLY_S ? ns - s0 : APPLY_S;
+    const bool last = s0 + APPLY_S >= ns;
+    const uint32_t valid = (1u << sc) - 1u;  // spiders of this pass
+    uint32_t lo[TAB ? 1 : APPLY_S], hi[TAB ? 1 : APPLY_S];
+    if constexpr (TAB) {
+      if (s0) __syncthreads();  // every wavefront is through with the tables
+      // thread: word jj of all entries whose upper two bits are its own
+      for (int i = threadIdx.x; i < APPLY_S * W; i += BS) {
+        const int q4 = i / W, jj = i - q4 * W, g = q4 >> 2, up = q4 & 3;
+        uint64_t v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int s = s0 + 4 * g + q;
+          const uint64_t rv = row_ptr(c, c.slist[s < ns ? s : 0])[jj];
+          v[q] = s < ns ? rv : 0;
+        }
+        const uint64_t u = ((up & 1) ? v[2] : 0) ^ ((up & 2) ? v[3] : 0);
+        LDSP uint64_t* e = c.scr + (16 * g + 4 * up) * W1 + jj;
+        e[0] = u;
+        e[W1] = u ^ v[0];
+        e[2 * W1] = u ^ v[1];
+        e[3 * W1] = u ^ v[0] ^ v[1];
+      }
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int q = 0; q < APPLY_S; ++q) {
+        const uint64_t v = row_ptr(c, __builtin_amdgcn_readlane(xs, s0 + q < ns ? s0 + q : s0))[j];
+        lo[q] = q < sc ? (uint32_t)v : 0;
+        hi[q] = q < sc ? (uint32_t)(v >> 32) : 0;
+      }
+    }
+    for (int base = r0; base < r1; base += 64) {
+      // one lane per row
+      const int w = base + lane < n ? base + lane : n - 1;
+      const uint64_t live = c.alive[w >> 6] & ~c.sel[w >> 6];
+      const bool act = base + lane < r1 && (((uint32_t)(live >> (w & 32)) >> (w & 31)) & 1);
+      uint32_t hit = 0;
+      int dk = 0;
+      const LDSP uint32_t* aw = a32 + (w >> 5);
+#pragma unroll
+      for (int g = 0; g < APPLY_S; g += 4) {
+        if (g >= sc) break;
+        uint32_t x[4], y[4] = {0, 0, 0, 0};
+        int kq[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int s = s0 + g + q < 63 ? s0 + g + q : 63;  // lanes past ns name the first spider, with no phase
+          x[q] = aw[2 * ldw * __builtin_amdgcn_readlane(nb, s)];
+          kq[q] = __builtin_amdgcn_readlane(kx, s);
+          // the spider's own row now holds its partner's neighbours
+          if (pivot) y[q] = aw[2 * ldw * __builtin_amdgcn_readlane(xs, s)];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t b = (x[q] >> (w & 31)) & 1u;
+          hit |= b << (g + q);
+          dk += (int)b * kq[q];
+          if (pivot) dk += 2 * (int)(b & (y[q] >> (w & 31)) & (valid >> (g + q)));  // adjacent to both ends
+        }
+      }
+      hit &= valid;
+      if (act && (dk & 7)) c.k[w] = (int8_t)((c.k[w] + dk) & 7);
+      hit = act ? hit | 0x80000000u : 0;
+      // WL words of a row per lane
+      const int rows = r1 - base < 64 ? r1 - base : 64;
+      LDSP uint64_t* rp = c.adj + (base + rr) * ldw + j;
+      for (int st = 0; st < rows; st += APPLY_U * rpw, rp += APPLY_U * rpw * ldw) {
+        uint32_t hm[APPLY_U];
+        uint64_t v[APPLY_U][WL];
+#pragma unroll
+        for (int u = 0; u < APPLY_U; ++u) {
+          hm[u] = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (st + u * rpw + rr), (int)hit);
+          const LDSP uint64_t* q = rp + u * rpw * ldw;
+          q = q < last_row ? q : last_row;  // rows past the last: read it, write nothing
+          v[u][0] = q[0];
+          if constexpr (WL == 2) v[u][1] = q[two ? 1 : 0];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (TAB) {
+          uint64_t e[APPLY_U][2][WL];
+#pragma unroll
+          for (int u = 0; u < APPLY_U; ++u)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              const LDSP uint64_t* q = c.scr + (int)(16 * g + __builtin_amdgcn_ubfe(hm[u], 4 * g, 4)) * W1 + j;
+              e[u][g][0] = q[0];
+              if constexpr (WL == 2) e[u][g][1] = q[1];
+            }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int u = 0; u < APPLY_U; ++u)
+#pragma unroll
+            for (int x = 0; x < WL; ++x) {
+              const uint32_t l = __builtin_amdgcn_bitop3_b32((uint32_t)v[u][x], (uint32_t)e[u][0][x], (uint32_t)e[u][1][x], 0x96);
+              const uint32_t h = __builtin_amdgcn_bitop3_b32((uint32_t)(v[u][x] >> 32), (uint32_t)(e[u][0][x] >> 32),
+                                                             (uint32_t)(e[u][1][x] >> 32), 0x96);
+              v[u][x] = ((uint64_t)h << 32) | l;
+            }
+        } else {
+#pragma unroll
+          for (int u = 0; u < APPLY_U; ++u) {
+            uint32_t l = (uint32_t)v[u][0], h = (uint32_t)(v[u][0] >> 32);
+#pragma unroll
+            for (int q = 0; q < APPLY_S; ++q) {
+              const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)hm[u], q, 1);
+              l = xor_and(l, lo[q], m);
+              h = xor_and(h, hi[q], m);
+            }
+            v[u][0] = ((uint64_t)h << 32) | l;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < APPLY_U; ++u) {
+          if (on && st + u * rpw + rr < rows && (hm[u] >> 31)) {
+            LDSP uint64_t* q = rp + u * rpw * ldw;
+#pragma unroll
+            for (int x = 0; x < WL; ++x) {
+              const uint64_t z = last ? v[u][x] & keep[x] : v[u][x];
+              if (x == 0 || two) {
+                q[x] = z;
+                pc += last ? __popcll(z) : 0;
+              }
+            }
+          }
+        }
+      }
+      // the diagonal: a row's own bit came in with each contribution
+      if (last && act) {
+        LDSP uint32_t* d = (LDSP uint32_t*)c.adj + 2 * ldw * w + (w >> 5);
+        const uint32_t x = *d, bit = 1u << (w & 31);
+        pc -= (x & bit) ? 1 : 0;
+        *d = x & ~bit;
+      }
+    }
+  }
+  const int tot = __builtin_amdgcn_readlane(wave_sum_lane63(pc), 63);
+  if (lane == 0) block_add(&sh.acc64[3], tot);
+  __syncthreads();
+}
+
+template <int BS>
+__device__ void apply_round_lds(Ctx<true>& c, Shared& sh, bool pivot) {
+  if (c.W >= APPLY_TAB_W && c.scr_words >= apply_tab_words(c.W)) apply_rows_lds<BS, true>(c, sh, pivot);
+  else apply_rows_lds<BS, false>(c, sh, pivot);
+}
+
 // Returns true when the selected columns were already dropped from the rows.
 template <int BS, bool LA>
 __device__ bool apply_round(Ctx<LA>& c, Shared& sh, bool pivot) {
   if constexpr (!LA) {
     if constexpr (BS >= 256) {
       if (c.tb && uni(sh.ns) <= TEAM_MAXS && c.scr_words >= TEAM_SLICE_LDS) {
-        apply_round_team<BS>(c, sh, pivot);
+        apply_round_team<BS>(sh, pivot);
         return true;
       }
     }
     if (uni(sh.ns) <= SPIDER_MAJOR_MAX && c.scr_words >= 64) {
-      apply_round_arena<BS>(c, sh, pivot);
+      apply_round_arena<BS>(sh, pivot);
+      return true;
+    }
+  }
+  if constexpr (LA) {
+    if (uni(sh.ns) <= SPIDER_MAJOR_MAX) {
+      apply_round_lds<BS>(c, sh, pivot);
       return true;
     }
   }
@@ -1184,10 +1467,14 @@ __device__ bool apply_round(Ctx<LA>& c, Shared& sh, bool pivot) {
   return false;
 }
 
-// Delete the selected spiders: clear their columns in every other row, zero
-// their rows, clear alive, phase 0.
-template <int BS, bool LA>
-__device__ void delete_selected(Ctx<LA>& c, Shared& sh, bool cols_done) {
+// The end of a round: delete the selected spiders (clear their columns in
+// every other row unless the update did, zero their rows, clear alive, phase
+// 0), undo a pivot round's partners, and bring scalar and counters up to date
+// (the edge count after the round comes from apply_round: sh.acc64[3] = twice
+// the count).  NEXT_LC: list the next local-complementation round's
+// candidates as well.  One barrier.
+template <int BS, bool LA, bool NEXT_LC>
+__device__ void end_round(Ctx<LA>& c, Shared& sh, bool cols_done, bool pivot, int removed) {
   const int W = c.W, n = c.n, nsw = uni(sh.nsw);
   const LDSP int32_t* sw = (const LDSP int32_t*)c.blocked;
   if (nsw > 0 && !cols_done) {
@@ -1205,19 +1492,23 @@ __device__ void delete_selected(Ctx<LA>& c, Shared& sh, bool cols_done) {
     const int x = c.slist[i];
     auto rx = row_ptr(c, x);
     for (int j = c.tl; j < W; j += c.T) rx[j] = 0;
-    if (c.tl == 0) c.k[x] = 0;
+    if (c.tl == 0) {
+      c.k[x] = 0;
+      if (pivot) c.partner[x] = -1;
+    }
     for (int q = c.tl; q < c.pw; q += c.T) c.par[(int64_t)x * c.pw + q] = 0;
   }
   // (the column pass above reads the selected set, not the present one)
-  for (int j = threadIdx.x; j < W; j += BS) c.alive[j] &= ~c.sel[j];
-  __syncthreads();
-}
-
-// Scalar and counters after a ZX round; the edge count after the round comes
-// from apply_round (sh.acc64[3] = twice the count).
-template <int BS, bool LA>
-__device__ void finish_round(Ctx<LA>& c, Shared& sh, int removed) {
-  if (threadIdx.x == 0) {
+  if (NEXT_LC) {
+    // the next round's candidates, with the present set's words by the same wavefront
+    lc_candidates<BS, LA, true>(c);
+    __builtin_amdgcn_wave_barrier();
+    for (int j = threadIdx.x >> 6; j < W; j += BS / 64)
+      if ((threadIdx.x & 63) == 0) c.alive[j] &= ~c.sel[j];
+  } else {
+    for (int j = threadIdx.x; j < W; j += BS) c.alive[j] &= ~c.sel[j];
+  }
+  if (threadIdx.x == BS - 1) {
     const int64_t e_before = sh.E;
     const int64_t e_after = sh.acc64[3] / 2;
     sh.pow_sqrt2 += (e_after - e_before) + removed;
@@ -1226,6 +1517,7 @@ __device__ void finish_round(Ctx<LA>& c, Shared& sh, int removed) {
     const int64_t others_before = e_before - sh.acc64[0];
     sh.fill_in += (sh.acc64[1] + (e_after - others_before)) / 2;
     sh.E = e_after;
+    sh.round++;
   }
   __syncthreads();
 }
@@ -1291,7 +1583,8 @@ __device__ __forceinline__ bool par_nonzero(const uint64_t* par, int pw, int v) 
 // Reads only phases, partners and parameter rows of the selected spiders,
 // none of which the round has changed yet.
 template <int BS, bool LA>
-__device__ __noinline__ void terms_round(Ctx<LA>& c, Shared& sh, bool pivot) {
+__device__ __noinline__ void terms_round(Shared& sh, bool pivot) {
+  const Ctx<LA> c = load_ctx<BS, LA>(sh);
   if (!c.pw) return;
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x, pw = c.pw, ns = uni(sh.ns);
@@ -1354,7 +1647,8 @@ __device__ __noinline__ void terms_round(Ctx<LA>& c, Shared& sh, bool pivot) {
 // thread per (present unselected row, parameter word); runs before the
 // round changes any unselected row (selected columns are still set).
 template <int BS, bool LA>
-__device__ __noinline__ void param_round(Ctx<LA>& c, Shared& sh, bool pivot) {
+__device__ __noinline__ void param_round(Shared& sh, bool pivot) {
+  const Ctx<LA> c = load_ctx<BS, LA>(sh);
   if (!c.pw) return;
   const int pw = c.pw, n = c.n, nsw = uni(sh.nsw);
   const LDSP int32_t* sw = (const LDSP int32_t*)c.blocked;
@@ -1548,7 +1842,8 @@ __device__ __forceinline__ void tiny_rounds(Tiny& st, int n, int32_t* trace, int
 // The rounds only, from and back to the LDS state (for callers that keep
 // the rest of the pipeline in LDS).
 template <int BS>
-__device__ __noinline__ void simplify_rounds_tiny(Ctx<true>& c, Shared& sh, int max_rounds) {
+__device__ __noinline__ void simplify_rounds_tiny(Shared& sh, int max_rounds) {
+  const Ctx<true> c = load_ctx<BS, true>(sh);
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x, n = c.n;
     const bool mine = lane < n;
@@ -1587,10 +1882,11 @@ __device__ __noinline__ void simplify_rounds_tiny(Ctx<true>& c, Shared& sh, int 
 // LEARN: candidates taken in the network's priority order (pol), else the
 // canonical order.
 template <int BS, bool LA, bool LEARN>
-__device__ void simplify_rounds(Ctx<LA>& c, Shared& sh, Pol* pol, int max_rounds) {
+__device__ __forceinline__ void simplify_rounds(Ctx<LA>& c, Shared& sh, Pol* pol, int max_rounds) {
+  save_ctx(c, sh);
   if constexpr (LA && !LEARN) {
     if (c.W == 1 && c.pw == 0) {
-      simplify_rounds_tiny<BS>(c, sh, max_rounds);
+      simplify_rounds_tiny<BS>(sh, max_rounds);
       return;
     }
   }
@@ -1598,24 +1894,24 @@ __device__ void simplify_rounds(Ctx<LA>& c, Shared& sh, Pol* pol, int max_rounds
   // here would be a defect, reported instead of looping on
   const int round_cap = uni(sh.round) + c.n + 1;
   // local-complementation rounds
+  if constexpr (!LEARN) {
+    lc_candidates<BS, LA, false>(c);
+    __syncthreads();
+  }
   for (;;) {
     if (max_rounds > 0 && uni(sh.round) >= max_rounds) return;
     if (uni(sh.round) > round_cap) {
       sh.status = ZX_EDEVICE;
       return;
     }
-    if (!build_candidates<BS, LA>(c, sh, 0)) break;
     if constexpr (LEARN) {
+      if (!build_candidates<BS, LA>(c, sh, 0)) break;
       const int C = list_lc<BS, LA>(c, sh, *pol);
       const float invN = pauli_mask_and_scale<BS, LA>(c, sh);
       policy_score<BS, LA>(c, *pol, C, invN, false);
       __syncthreads();
       sort_keys_desc<BS>(*pol, C);
       select_lc_priority<BS, LA>(c, sh, *pol, C);
-    } else {
-      lfmis<BS, LA>(c, sh);  // also counts, traces and lists the set
-    }
-    if constexpr (LEARN) {
       if (threadIdx.x == 0) sh.cnt = 0;
       __syncthreads();
       int cnt = 0;
@@ -1623,17 +1919,18 @@ __device__ void simplify_rounds(Ctx<LA>& c, Shared& sh, Pol* pol, int max_rounds
       if (cnt) atomicAdd(&sh.cnt, cnt);
       __syncthreads();
       trace_lc_round<BS, LA>(c, sh);
+      prepare_round<BS, LA>(c, sh, false, false);
+    } else {
+      select_lc<BS, LA>(c, sh);
+      if (uni(sh.ns) == 0) break;
     }
     const int removed = uni(sh.cnt);
-    prepare_round<BS, LA>(c, sh, false, !LEARN);
     if (c.pw) {
-      terms_round<BS, LA>(c, sh, false);
-      param_round<BS, LA>(c, sh, false);
+      terms_round<BS, LA>(sh, false);
+      param_round<BS, LA>(sh, false);
     }
     const bool cc = apply_round<BS, LA>(c, sh, false);
-    delete_selected<BS, LA>(c, sh, cc);
-    if (threadIdx.x == 0) sh.round++;  // published by finish_round's barrier
-    finish_round<BS, LA>(c, sh, removed);
+    end_round<BS, LA, !LEARN>(c, sh, cc, false, removed);
   }
   // pivot rounds
   for (;;) {
@@ -1657,14 +1954,11 @@ __device__ void simplify_rounds(Ctx<LA>& c, Shared& sh, Pol* pol, int max_rounds
     if (npairs == 0) break;
     prepare_round<BS, LA>(c, sh, true, true);  // lists built with the selection
     if (c.pw) {
-      terms_round<BS, LA>(c, sh, true);
-      param_round<BS, LA>(c, sh, true);
+      terms_round<BS, LA>(sh, true);
+      param_round<BS, LA>(sh, true);
     }
     const bool cc = apply_round<BS, LA>(c, sh, true);
-    delete_selected<BS, LA>(c, sh, cc);
-    for (int i = threadIdx.x; i < uni(sh.ns); i += BS) c.partner[c.slist[i]] = -1;
-    if (threadIdx.x == 0) sh.round++;  // both published by finish_round's barrier
-    finish_round<BS, LA>(c, sh, 2 * npairs);
+    end_round<BS, LA, false>(c, sh, cc, true, 2 * npairs);
   }
 }
 
@@ -1783,13 +2077,13 @@ struct SimpArgs {
 // place; every other row holding the column is reduced and counted).  The
 // arena ends as run_diagram leaves it.
 template <int BS>
-__device__ __noinline__ void run_tiny(uint8_t* arena, const SimpArgs& a, Shared& sh) {
+__device__ __noinline__ void run_tiny(uint8_t* arena, bool resume, int max_rounds, bool extract, Shared& sh) {
   ZxHeader* h = (ZxHeader*)arena;
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
     const int n = h->n, q = h->n_out;
     const bool mine = lane < n;
-    const bool src = !a.resume;
+    const bool src = !resume;
     const uint64_t* adj0 = (const uint64_t*)(arena + (src ? h->off_src_adj : h->off_adj));
     const int8_t* ph0 = (const int8_t*)(arena + (src ? h->off_src_phase : h->off_phase));
     const int32_t* outs = (const int32_t*)(arena + h->off_out);
@@ -1808,7 +2102,7 @@ __device__ __noinline__ void run_tiny(uint8_t* arena, const SimpArgs& a, Shared&
     int pc = __popcll(st.row);
     for (int o = 32; o > 0; o >>= 1) pc += __shfl_xor(pc, o, 64);
     st.E = pc / 2;
-    tiny_rounds(st, n, (int32_t*)(arena + h->off_trace), a.max_rounds);
+    tiny_rounds(st, n, (int32_t*)(arena + h->off_trace), max_rounds);
     // CURRENT section and header
     if (mine) {
       ((uint64_t*)(arena + h->off_adj))[lane] = st.row;
@@ -1827,7 +2121,7 @@ __device__ __noinline__ void run_tiny(uint8_t* arena, const SimpArgs& a, Shared&
     }
     int rank = -1;
     int64_t ops = 0;
-    if (a.extract && q > 0) {
+    if (extract && q > 0) {
       // output frontier: row r = the row of output r's spider, present
       // columns not attached to an output
       uint64_t om = 0;
@@ -1878,13 +2172,22 @@ __device__ __noinline__ void run_tiny(uint8_t* arena, const SimpArgs& a, Shared&
   __syncthreads();
 }
 
+// The LDS from `used` bytes to the budget, for the round updates.
+template <bool LA>
+__device__ __forceinline__ void set_scratch(Ctx<LA>& c, uint8_t* lds, int64_t used, int64_t cap) {
+  uint8_t* at = align16(lds + used);
+  const int64_t free_bytes = cap - (int64_t)(at - lds);
+  c.scr = (LDSP uint64_t*)at;
+  c.scr_words = free_bytes > 0 ? (int)(free_bytes / 8) : 0;
+}
+
 // One diagram, start to finish, with the adjacency in LDS (LA) or the arena.
 template <int BS, bool LA, bool LEARN>
-__device__ void run_diagram(uint8_t* arena, uint8_t* lds, const SimpArgs& a, Shared& sh) {
+__device__ __forceinline__ void run_diagram(uint8_t* arena, uint8_t* lds, const SimpArgs& a, Shared& sh) {
   ZxHeader* h = (ZxHeader*)arena;
   if constexpr (LA && !LEARN) {
     if (uni(h->W) == 1 && uni(h->pw) == 0) {
-      run_tiny<BS>(arena, a, sh);
+      run_tiny<BS>(arena, a.resume != 0, a.max_rounds, a.extract != 0, sh);
       return;
     }
   }
@@ -1900,14 +2203,11 @@ __device__ void run_diagram(uint8_t* arena, uint8_t* lds, const SimpArgs& a, Sha
   if constexpr (LEARN)
     setup_pol<BS>(pol, lds + (LA ? lds_adj_bytes(c.n, c.W) : 0) + aux_bytes(c.n, c.W), c.n, a.wbf,
                   a.param);
-  if constexpr (!LA) {
-    // the LDS the auxiliary arrays (and the policy areas) leave free
-    const int64_t used = aux_bytes(c.n, c.W) + (LEARN ? pol_bytes(c.n, BS) : 0);
-    uint8_t* at = align16(lds + used);
-    const int64_t free_bytes = a.lds_cap - (int64_t)(at - lds);
-    c.scr = (LDSP uint64_t*)at;
-    c.scr_words = free_bytes > 0 ? (int)(free_bytes / 8) : 0;
-    c.tb = c.W <= TEAM_MAXW ? a.tb : nullptr;
+  {
+    // the LDS that the adjacency, the auxiliary arrays and the policy areas leave free
+    const int64_t used = (LA ? lds_adj_bytes(c.n, c.W) : 0) + aux_bytes(c.n, c.W) + (LEARN ? pol_bytes(c.n, BS) : 0);
+    set_scratch(c, lds, used, a.lds_cap);
+    if constexpr (!LA) c.tb = c.W <= TEAM_MAXW ? a.tb : nullptr;
   }
   simplify_rounds<BS, LA, LEARN>(c, sh, &pol, a.max_rounds);
   store_state<BS, LA>(c, sh);
@@ -1947,12 +2247,7 @@ __device__ int64_t greedy_cost(uint8_t* arena, uint8_t* lds, const SimpArgs& a, 
   c.par = nullptr;
   c.terms = nullptr;
   load_state<BS, LA>(c, sh, true);
-  if constexpr (!LA) {
-    uint8_t* at = align16(lds + aux_bytes(c.n, c.W));
-    const int64_t free_bytes = a.lds_cap - (int64_t)(at - lds);
-    c.scr = (LDSP uint64_t*)at;
-    c.scr_words = free_bytes > 0 ? (int)(free_bytes / 8) : 0;
-  }
+  set_scratch(c, lds, (LA ? lds_adj_bytes(c.n, c.W) : 0) + aux_bytes(c.n, c.W), a.lds_cap);
   simplify_rounds<BS, LA, false>(c, sh, nullptr, 0);
   int64_t rowops = 0;
   if (a.extract && c.q_out > 0) {
@@ -1967,7 +2262,7 @@ __device__ int64_t greedy_cost(uint8_t* arena, uint8_t* lds, const SimpArgs& a, 
 }
 
 template <int BS, bool LEARN>
-__device__ void process_diagram(uint8_t* arena, uint8_t* lds, const SimpArgs& a, Shared& sh) {
+__device__ __forceinline__ void process_diagram(uint8_t* arena, uint8_t* lds, const SimpArgs& a, Shared& sh) {
   ZxHeader* h = (ZxHeader*)arena;
   const int n = uni(h->n), W = uni(h->W);
   const int64_t aux_g = aux_bytes(n, W);
@@ -2228,12 +2523,7 @@ __global__ __launch_bounds__(BS) void rollout_kernel(Queue* q, RollArgs a) {
       // the candidate as a one-rewrite round, then the greedy schedule
       prepare_round<BS, true>(c, sh, piv, false);
       const bool cc = apply_round<BS, true>(c, sh, piv);
-      delete_selected<BS, true>(c, sh, cc);
-      finish_round<BS, true>(c, sh, piv ? 2 : 1);
-      if (piv) {
-        for (int i = tid; i < uni(sh.ns); i += BS) c.partner[c.slist[i]] = -1;
-        __syncthreads();
-      }
+      end_round<BS, true, false>(c, sh, cc, piv, piv ? 2 : 1);
       simplify_rounds<BS, true, false>(c, sh, nullptr, 0);
       if (c.q_out > 0) {
         frontier<BS, true>(c, sh, a.mbuf + (int64_t)blockIdx.x * a.mbuf_words, true, false);
@@ -2600,12 +2890,12 @@ __global__ __launch_bounds__(BS) void single_rewrite_kernel(uint8_t* arena, int3
     if (threadIdx.x == 0) sh.E = e;
     __syncthreads();
   } else {
+    save_ctx(c, sh);
     prepare_round<BS, LA>(c, sh, pivot != 0, false);
-    terms_round<BS, LA>(c, sh, pivot != 0);
-    param_round<BS, LA>(c, sh, pivot != 0);
+    terms_round<BS, LA>(sh, pivot != 0);
+    param_round<BS, LA>(sh, pivot != 0);
     const bool cc = apply_round<BS, LA>(c, sh, pivot != 0);
-    delete_selected<BS, LA>(c, sh, cc);
-    finish_round<BS, LA>(c, sh, pivot ? 2 : 1);
+    end_round<BS, LA, false>(c, sh, cc, pivot != 0, pivot ? 2 : 1);
   }
   store_state<BS, LA>(c, sh);
 }

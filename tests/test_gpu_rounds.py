@@ -1,0 +1,54 @@
+"""Round updates with the adjacency in LDS against the oracle: row widths on
+both sides of the table threshold, diagrams that leave no room for the
+tables, rounds of more than 8 and of more than 64 rewrites, rounds of pivots
+only, through the variants whose LDS budgets put the same diagram in LDS or
+in the arena."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import make_diagram
+from workloads.generators import Diagram
+
+pytestmark = pytest.mark.gpu
+
+# (spiders, qubits, density): 128/129 words edge, 6/7 words (tables from 7),
+# 1060..1088 spiders fill the 152 KiB budget up to the last table's place,
+# sparse ones have rounds of many rewrites
+SIZES = [(65, 4, 0.2), (129, 6, 0.02), (384, 8, 0.3), (385, 8, 0.3), (447, 9, 0.004), (700, 12, 0.005),
+         (1024, 16, 0.1), (1060, 16, 0.2), (1075, 16, 0.2), (1088, 16, 0.3)]
+
+
+def diagram(seed, n, q, p, pauli):
+    d = make_diagram(seed, n, q, n, p)
+    if pauli:  # every phase 0 or pi: the first round is a pivot round
+        d = Diagram(n=n, adj=d.adj, phase=(d.phase & 4).astype(np.int8), inputs=d.inputs, outputs=d.outputs,
+                    bnd_is_h=d.bnd_is_h)
+    return d
+
+
+@pytest.mark.parametrize("pauli", [False, True])
+@pytest.mark.parametrize("n,q,p", SIZES)
+def test_round_updates(zx, n, q, p, pauli):
+    d = diagram(71, n, q, p, pauli)
+    og = oracle.Graph.from_diagram(d)
+    assert og.simplify() == oracle.OK
+    M, fp, rank, ops = og.frontier()
+    names = zx.simplify_variants()
+    for v, name in enumerate(names):
+        if name.startswith("bs64") and n > 400:
+            continue  # one wavefront: minutes of rounds add nothing
+        g = zx.Graph.from_diagram(d)
+        print("round updates", n, p, pauli, name, flush=True)
+        try:
+            zx.simplify([g], tune_id=v)
+        except zx.ZxError as e:
+            assert e.code == zx.ZX_ECAPACITY
+            continue
+        adj, ph, al, info = g.read()
+        assert info.status == 0
+        assert np.array_equal(al, og.alive) and np.array_equal(ph, og.k) and np.array_equal(adj, og.adj), name
+        assert info.pow_sqrt2 == og.scalar.pow_sqrt2 and info.phase8 == og.scalar.phase8 % 8
+        assert info.fill_in == og.scalar.fill_in and info.rank == rank and info.rowops == ops
+        np.testing.assert_array_equal(g.trace(), og.trace)
+        assert np.array_equal(g.frontier()[0], M)
