@@ -227,7 +227,9 @@ typedef struct {
 } zx_simplify_opts;
 
 /* Number of kernel variants and a short description of variant id
- * ("bs<threads>-lds<KiB>k").  The one-wavefront variant (bs64) runs the
+ * ("bs<threads>-lds<KiB>k", or "by-size": a launch per run of sizes, each
+ * with the LDS budget its diagrams need; the default of a greedy batch).  The
+ * one-wavefront variant (bs64) runs the
  * greedy schedule only: with ZX_POLICY_LEARNED it is refused as too small
  * (ZX_ECAPACITY).  Without a tune_id, a batch of up to 256 diagrams of at
  * most 64 spiders takes it; such diagrams without parameters run their

@@ -1185,7 +1185,7 @@ __device__ __forceinline__ uint32_t xor_and(uint32_t x, uint32_t y, uint32_t z) 
 constexpr int APPLY_S = 8;
 constexpr int APPLY_U = 4;
 constexpr int APPLY_TAB_W = 7;
-__device__ __forceinline__ int apply_tab_words(int W) { return APPLY_S / 4 * 16 * (W + 2); }
+__host__ __device__ __forceinline__ int apply_tab_words(int W) { return APPLY_S / 4 * 16 * (W + 2); }
 
 template <int BS, bool TAB>
 __device__ __forceinline__ void apply_rows_lds(Ctx<true>& c, Shared& sh, bool pivot) {
@@ -2961,8 +2961,10 @@ const Variant kVariants[] = {
     {256, 96 * 1024, "bs256-lds96k"},   {256, 152 * 1024, "bs256-lds152k"},
     {512, 64 * 1024, "bs512-lds64k"},   {512, 152 * 1024, "bs512-lds152k"},
     {64, 32 * 1024, "bs64-lds32k"},  // one wavefront: greedy schedule, small diagrams
+    {512, 152 * 1024, "by-size"},    // a launch per run of sizes (plan_segments); else as bs512-lds152k
 };
 constexpr int kOneWaveVariant = 6;
+constexpr int kBySizeVariant = 7;
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int kDefaultVariant = 1;
 
@@ -3108,6 +3110,72 @@ static int32_t team_prefix(const int32_t* sizes, int32_t n_graphs) {
   return best;
 }
 
+// A run of the sorted batch launched with one variant.
+struct Segment {
+  int variant;
+  int32_t begin, count;
+};
+
+// LDS a diagram's greedy run in LDS asks for, with the update's tables.
+static int64_t lds_need(int n) {
+  const int W = (n + 63) / 64;
+  return lds_adj_bytes(n, W) + aux_bytes(n, W) + 16 + (W >= APPLY_TAB_W ? 8 * (int64_t)apply_tab_words(W) : 0);
+}
+
+// Launches for the diagrams begin .. n-1 of a batch sorted by falling size.  A
+// workgroup holds its variant's LDS budget whatever its diagram needs, so a
+// batch of uneven sizes runs its large diagrams with 152 KiB (one workgroup a
+// CU), the middle ones with 64 KiB (two) and the small ones with 32 KiB
+// (four), one launch after the other, wherever that beats fewer launches by
+// this model: a launch lasts as long as its largest diagram, or its diagrams'
+// times spread over the resident workgroups.  Times of one diagram alone
+// (us, measured 128 spiders: 83, 256: 150, 512: 332, 1024: 877; arena mode
+// 1440: 6400), longer by 5 % and 25 % with two and four on a CU.  4096
+// diagrams of 4-64 qubits: 3.9 ms with 152 KiB for all, 3.0 with 64 KiB, 2.7
+// in three launches; of 4-24 qubits: 1.4, 0.79, 0.47 with 32 KiB.
+static std::vector<Segment> plan_segments(const std::vector<int32_t>& sizes, int32_t begin, int n_cu) {
+  const int32_t n = (int32_t)sizes.size();
+  struct Budget { int variant, per_cu; double slow; };
+  const Budget budgets[3] = {{5, 1, 1.0}, {4, 2, 1.05}, {0, 4, 1.25}};
+  auto alone = [](int m) {
+    const double x = m / 1000.0;
+    return lds_need(m) <= kVariants[5].lds_cap ? m * (0.55 + 0.3 * x) : 2230.0 * x * x * x;
+  };
+  // first diagram of the sorted run that a budget takes in LDS
+  int32_t first[3];
+  for (int k = 0; k < 3; ++k) {
+    first[k] = begin;
+    if (k > 0)
+      while (first[k] < n && lds_need(sizes[first[k]]) > kVariants[budgets[k].variant].lds_cap) ++first[k];
+  }
+  std::vector<double> sum((size_t)(n - begin) + 1, 0.0);
+  for (int32_t i = begin; i < n; ++i) sum[i - begin + 1] = sum[i - begin] + alone(sizes[i]);
+  std::vector<Segment> best;
+  double best_t = 1e300;
+  for (int use = 1; use < 8; ++use) {  // budgets used, as bits
+    std::vector<Segment> seg;
+    double t = 0;
+    int32_t end = n;
+    bool ok = true;
+    for (int k = 2; k >= 0; --k) {
+      if (!((use >> k) & 1)) continue;
+      // this budget's run: from where it fits up to the smaller budgets'
+      const int32_t b = (use & ((1 << k) - 1)) ? std::min(first[k], end) : begin;
+      ok = ok && b >= first[k];
+      if (b < end) {
+        seg.insert(seg.begin(), Segment{budgets[k].variant, b, end - b});
+        t += budgets[k].slow * std::max(alone(sizes[b]), (sum[end - begin] - sum[b - begin]) / (n_cu * budgets[k].per_cu)) + 5.0;
+      }
+      end = b;
+    }
+    if (ok && t < best_t) {
+      best_t = t;
+      best = seg;
+    }
+  }
+  return best;
+}
+
 struct zx_batch {
   uint8_t** table_dev;  // in the workspace
   Queue* queue;         // in the workspace
@@ -3118,7 +3186,16 @@ struct zx_batch {
   double mean_n;
   int32_t tuned;        // autotuned variant, -1 if none
   int32_t n_big;        // the first n_big diagrams (largest first) run with teams
+  std::vector<Segment> segments;  // the by-size launches of the others
 };
+
+static zx_status launch_segments(const zx_batch* b, const std::vector<Segment>& segs, const SimpArgs& a, hipStream_t s) {
+  for (const Segment& g : segs) {
+    const zx_status st = launch_simplify(g.variant, b->table_dev + g.begin, g.count, b->queue, a, false, s);
+    if (st != ZX_OK) return st;
+  }
+  return ZX_OK;
+}
 
 extern "C" int32_t zx_simplify_variants(void) { return kNumVariants; }
 extern "C" const char* zx_simplify_variant_name(int32_t id) {
@@ -3165,6 +3242,7 @@ extern "C" zx_status zx_batch_prepare(zx_batch** b, zx_graph* const* graphs, int
   B->tuned = -1;
   // diagrams whose arena-mode rounds a team of workgroups shares
   B->n_big = team_prefix(B->sizes.data(), n_graphs);
+  if (const ZxDevice* d = zx_device()) B->segments = plan_segments(B->sizes, B->n_big, d->n_cu);
   hipError_t e = hipMemcpyAsync(B->table_dev, B->arenas.data(), (size_t)n_graphs * 8,
                                 hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -3214,6 +3292,7 @@ static int pick_variant(const zx_batch* b, int tune_id, bool learned) {
     // a few diagrams of at most 64 spiders run in one wavefront's registers:
     // one-wave workgroups, each on its own CU
     if (b->max_n <= 64 && b->n <= 256 && variant_fits(b, kOneWaveVariant, false)) return kOneWaveVariant;
+    if (variant_fits(b, kBySizeVariant, false)) return kBySizeVariant;
   }
   const int v = pick_variant_n(b->max_n, learned);
   return v >= 0 ? v : kDefaultVariant;
@@ -3247,9 +3326,9 @@ int32_t zx_max_spiders(int32_t policy) {
   return best;
 }
 
-// Variant for a batch whose largest diagram has max_n spiders: 512-thread
-// workgroups; the 152 KiB budget when that diagram's adjacency then fits in
-// LDS, else 64 KiB (arena mode either way, and two workgroups per CU).
+// Variant for a learned batch whose largest diagram has max_n spiders (and
+// for a greedy one that no other rule takes): 512-thread workgroups; the 152
+// KiB budget when that diagram's adjacency then fits in LDS, else 64 KiB.
 static int pick_variant_n(int32_t max_n, bool learned) {
   const int W = (max_n + 63) / 64;
   const int64_t aux = aux_bytes(max_n, W) + (learned ? pol_bytes(max_n, 512) : 0);
@@ -3324,7 +3403,10 @@ extern "C" zx_status zx_batch_simplify(zx_batch* b, const zx_simplify_opts* o, h
     zx_status st = launch_teams(b->table_dev, n_big, simp_args(o), s);
     if (st != ZX_OK) return st;
   }
-  if (b->n > n_big) {
+  if (b->n > n_big && v == kBySizeVariant && !learned) {
+    zx_status st = launch_segments(b, b->segments, simp_args(o), s);
+    if (st != ZX_OK) return st;
+  } else if (b->n > n_big) {
     zx_status st = launch_simplify(v, b->table_dev + n_big, b->n - n_big, b->queue, simp_args(o), learned, s);
     if (st != ZX_OK) return st;
   }
@@ -3358,9 +3440,11 @@ extern "C" zx_status zx_batch_autotune(zx_batch* b, int32_t extract, int32_t rep
   const SimpArgs a = simp_args(&o);
   for (int v = 0; v < kNumVariants; ++v) {
     if (!variant_fits(b, v, false)) continue;
-    if (launch_simplify(v, b->table_dev, b->n, b->queue, a, false, s) != ZX_OK) continue;
+    const std::vector<Segment> segs = v == kBySizeVariant ? plan_segments(b->sizes, 0, zx_device()->n_cu)
+                                                          : std::vector<Segment>{{v, 0, b->n}};
+    if (launch_segments(b, segs, a, s) != ZX_OK) continue;
     ZX_HIP(hipEventRecord(e0, s));
-    for (int r = 0; r < reps; ++r) launch_simplify(v, b->table_dev, b->n, b->queue, a, false, s);
+    for (int r = 0; r < reps; ++r) launch_segments(b, segs, a, s);
     ZX_HIP(hipEventRecord(e1, s));
     ZX_HIP(hipEventSynchronize(e1));
     float ms = 0;

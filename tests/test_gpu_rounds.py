@@ -52,3 +52,26 @@ def test_round_updates(zx, n, q, p, pauli):
         assert info.fill_in == og.scalar.fill_in and info.rank == rank and info.rowops == ops
         np.testing.assert_array_equal(g.trace(), og.trace)
         assert np.array_equal(g.frontier()[0], M)
+
+
+@pytest.mark.parametrize("count,q_hi", [(1, 64), (257, 24), (1200, 64), (900, 72)])
+def test_by_size_equals_one_variant(zx, count, q_hi):
+    """Uneven batches in one to three launches by size (the default, its own
+    variant) leave every arena as one 64 KiB launch for all does."""
+    import torch
+    from workloads import batch_diagram
+    ds = [batch_diagram(81, i, q_hi=q_hi) for i in range(count)]
+    arenas = []
+    by_size = zx.simplify_variants().index("by-size")
+    for tune in (-1, by_size, zx.simplify_variants().index("bs512-lds64k")):
+        sizes = [(zx.Graph.bytes_for(d.n, d.qubits, d.qubits) + 255) // 256 * 256 for d in ds]
+        pool = torch.zeros(sum(sizes), dtype=torch.uint8, device="cuda")
+        offs = np.concatenate([[0], np.cumsum(sizes)])
+        gs = [zx.Graph.from_diagram(d, arena=pool[offs[i]:offs[i + 1]]) for i, d in enumerate(ds)]
+        print("by size", count, q_hi, tune, flush=True)
+        b = zx.Batch(gs)
+        b.run(tune_id=tune)
+        b.run(tune_id=tune)
+        assert b.status() == zx.ZX_OK
+        arenas.append(pool)
+    assert torch.equal(arenas[0], arenas[2]) and torch.equal(arenas[1], arenas[2])
