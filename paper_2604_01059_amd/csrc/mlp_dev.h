@@ -96,18 +96,4 @@ __device__ __forceinline__ float sum_hidden(float s[16], float b2) {
   return r[0] + __shfl_xor(r[0], 16, 64) + b2;
 }
 
-// Scores of 32 rows; element i of s is the score of row acc_row(i, lane)
-// (identical in the 32 lanes of a half-wave).
-__device__ inline void score32(bf16x8 a, const uint16_t* wbf, const float* param, float s[16]) {
-  hidden32<1>(a, wbf, param, s);
-  // sum over the 32 hidden units a half-wave holds, fixed butterfly order
-#pragma unroll
-  for (int o = 1; o < 32; o <<= 1)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] += __shfl_xor(s[i], o, 64);
-  const float b2 = param[P_B2];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) s[i] += b2;
-}
-
 }  // namespace zxmlp

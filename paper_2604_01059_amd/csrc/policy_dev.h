@@ -262,87 +262,67 @@ __device__ void pivot_features(Ctx<LA>& c, int u, int v, float invN, LDSP uint16
   }
 }
 
-typedef int pol_v8i __attribute__((ext_vector_type(8)));
-typedef float pol_v16f __attribute__((ext_vector_type(16)));
 
-// 32 bits as 32 FP4 (E2M1) operand values of a 64-deep matrix-core product:
-// nibble r of dword t is bit 4r + t (code 1 = 0.5, or 0).
-__device__ __forceinline__ pol_v8i bits_fp4(uint32_t d) {
-  pol_v8i o;
-  o[0] = (int)(d & 0x11111111u);
-  o[1] = (int)((d >> 1) & 0x11111111u);
-  o[2] = (int)((d >> 2) & 0x11111111u);
-  o[3] = (int)((d >> 3) & 0x11111111u);
-  o[4] = o[5] = o[6] = o[7] = 0;
-  return o;
-}
-
-// Two-hop counts of candidates list[base + r], r < 32 (entries past C count
-// nothing), into th[r] (one wavefront): the spiders v other than x and not
-// adjacent to x that share a neighbour with x.  A x A counts the common
-// neighbours of the 32 candidates and 32 spiders v at a time on the matrix
-// cores (v_mfma_scale_f32_32x32x64_f8f6f4: a bit is the FP4 value 0.5 scaled
-// by 2^1 to 1, every sum an exact fp32 count below 2^13).  Each block's
-// accumulator first takes -12288 at v = x and at v adjacent to x (one more
-// product: x's row with its own bit against a one-hot operand of value -6
-// scaled by 2^11), so a positive sum marks exactly a two-hop spider; one
-// ballot per accumulator register counts them per candidate.
+// Two-hop counts of entries list[0 .. cnt-1] into th[0 .. cnt-1] (one
+// wavefront): the spiders v other than x and not adjacent to x that share a
+// neighbour with x.  Lanes form groups of Wp (W rounded up to a power of
+// two), a candidate each; lane j of a group keeps word j of the present
+// spiders outside N[x] not reached yet, and the neighbours' rows, in ascending
+// order, take theirs out until none is left anywhere in the wavefront.  After
+// a few rounds a diagram's density is near one half and about log2(n) rows
+// reach everything; in a sparse one the neighbours are few.  (The product
+// A x A on the matrix cores does all n rows for all n spiders: scoring took
+// 60 k cycles a round at 640 spiders and 554 k at 1856; now @S6@ and @S18@.)
 template <bool LA>
-__device__ void two_hop32(Ctx<LA>& c, const LDSP uint32_t* list, int base, int C, LDSP int32_t* th) {
-  const int lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
-  const int n = c.n, W = c.W;
-  const int xr = base + l32 < C ? (int)list[base + l32] : -1;
-  const auto rx = row_ptr(c, xr < 0 ? 0 : xr);
-  int cnt[32];
+__device__ void two_hop(Ctx<LA>& c, const LDSP uint32_t* list, int cnt, LDSP int32_t* th) {
+  constexpr int Q = LA ? 4 : 8;  // rows in flight
+  const int lane = threadIdx.x & 63, W = c.W;
+  int Wp = 1;
+  while (Wp < W && Wp < 64) Wp <<= 1;
+  const int G = 64 / Wp, g = lane / Wp, j = lane & (Wp - 1);
+  const bool in0 = j < W, in1 = j + 64 < W;
+  const int j0 = in0 ? j : W - 1, j1 = in1 ? j + 64 : W - 1;
+  for (int b = 0; b < cnt; b += G) {
+    const bool has = b + g < cnt;
+    const int x = (int)list[has ? b + g : b];
+    const auto rx = row_ptr(c, x);
+    const uint64_t me = 1ull << (x & 63);
+    uint64_t l0 = has && in0 ? c.alive[j0] & ~rx[j0] & ~((x >> 6) == j0 ? me : 0) : 0;
+    uint64_t l1 = has && in1 ? c.alive[j1] & ~rx[j1] & ~((x >> 6) == j1 ? me : 0) : 0;
+    const int total = __popcll(l0) + __popcll(l1);
+    uint64_t next = rx[0];
+    for (int w = 0; w < W; ++w) {
+      const uint64_t cur = has ? next : 0;
+      next = rx[w + 1 < W ? w + 1 : w];
 #pragma unroll
-  for (int r = 0; r < 32; ++r) cnt[r] = 0;
-  for (int jb = 0; 32 * jb < n; ++jb) {
-    const int v = 32 * jb + l32;
-    const bool vin = v < n;
-    const auto rv = row_ptr(c, vin ? v : 0);
-    const int wj = jb >> 1;
-    uint64_t ax = rx[wj] & (xr >= 0 ? ~0ull : 0ull);
-    if (xr >= 0 && (xr >> 6) == wj) ax |= 1ull << (xr & 63);
-    pol_v8i bo = bits_fp4(h == (jb & 1) && vin ? 1u << l32 : 0u);
-    bo[0] *= 15;  // nibble 0xF: -6
-    bo[1] *= 15;
-    bo[2] *= 15;
-    bo[3] *= 15;
-    pol_v16f acc = {};
-    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bits_fp4((uint32_t)(ax >> (32 * h))), bo, acc, 4, 4, 0,
-                                                          128, 0, 138);
-    // rows rx and rv are always in range (row 0 stands in), so their words
-    // are loaded without branches, four steps' worth before the first is used
-    const uint32_t am = xr >= 0 ? 0xffffffffu : 0u, bm = vin ? 0xffffffffu : 0u;
-    int ks = 0;
-    for (; ks + 4 <= W; ks += 4) {
-      uint64_t ra[4], rb[4];
+      for (int half = 0; half < 2; ++half) {
+        uint32_t d = (uint32_t)(cur >> (32 * half));
+        while (__ballot(d != 0)) {
+          uint64_t v0[Q], v1[Q];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        ra[q] = rx[ks + q];
-        rb[q] = rv[ks + q];
+          for (int q = 0; q < Q; ++q) {
+            // a group that is through reads its own row, whose spiders are out already
+            const int u = d ? 64 * w + 32 * half + __builtin_ctz(d) : x;
+            const auto ru = row_ptr(c, u);
+            v0[q] = ru[j0];
+            v1[q] = W > 64 ? ru[j1] : 0;
+            d &= d - 1;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            l0 &= ~v0[q];
+            l1 &= ~v1[q];
+          }
+        }
+        if (!__ballot((l0 | l1) != 0)) break;
       }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bits_fp4((uint32_t)(ra[q] >> (32 * h)) & am),
-                                                              bits_fp4((uint32_t)(rb[q] >> (32 * h)) & bm), acc, 4,
-                                                              4, 0, 128, 0, 128);
+      if (!__ballot((l0 | l1) != 0)) break;
     }
-    for (; ks < W; ++ks)
-      acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bits_fp4((uint32_t)(rx[ks] >> (32 * h)) & am),
-                                                            bits_fp4((uint32_t)(rv[ks] >> (32 * h)) & bm), acc, 4, 4,
-                                                            0, 128, 0, 128);
-    // register r of lane (h, l32): candidate 8 (r / 4) + 4 h + r % 4, spider 32 jb + l32
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const uint64_t b = __ballot(acc[r] > 0.0f);
-      cnt[8 * (r >> 2) + (r & 3)] += __popcll(b & 0xffffffffull);
-      cnt[8 * (r >> 2) + 4 + (r & 3)] += __popcll(b >> 32);
-    }
+    int k = total - __popcll(l0) - __popcll(l1);
+    for (int o = 1; o < Wp; o <<= 1) k += __shfl_xor(k, o);
+    if (has && j == 0) th[b + g] = k;
   }
-#pragma unroll
-  for (int r = 0; r < 32; ++r)
-    if (lane == r) th[r] = cnt[r];
 }
 
 // Features of a block of up to 32 candidates (list entries base..base+cnt)
@@ -406,7 +386,7 @@ __device__ __forceinline__ uint32_t float_order(float x) {
 // Scores of list entries 0..C-1 into p.key as (order(score) << 32) |
 // ~index, so that descending keys give descending scores, ties by index.
 // pivot: the entries are edges; the two-hop counts of their first and
-// second ends come from two matrix-core passes over the endpoint list.
+// second ends come from two passes over the endpoint list.
 template <int BS, bool LA>
 __device__ void policy_score(Ctx<LA>& c, Pol& p, int C, float invN, bool pivot) {
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -421,10 +401,10 @@ __device__ void policy_score(Ctx<LA>& c, Pol& p, int C, float invN, bool pivot) 
       el[lane] = lane < 32 ? e >> 16 : e & 0xffffu;
       __builtin_amdgcn_s_waitcnt(0);
       __builtin_amdgcn_wave_barrier();
-      two_hop32(c, el, 0, cnt, tb);
-      two_hop32(c, el, 32, 32 + cnt, tb + 32);
+      two_hop(c, el, cnt, tb);
+      two_hop(c, el + 32, cnt, tb + 32);
     } else {
-      two_hop32(c, p.list, base, C, tb);
+      two_hop(c, p.list + base, cnt, tb);
     }
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
@@ -432,13 +412,11 @@ __device__ void policy_score(Ctx<LA>& c, Pol& p, int C, float invN, bool pivot) 
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
     float s[16];
-    zxmlp::score32(zxmlp::load_a(fb), p.wbf, p.param, s);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int idx = base + zxmlp::acc_row(i, lane);
-      if ((lane & 31) == i && idx < C)
-        p.key[idx] = ((uint64_t)float_order(s[i]) << 32) | (uint32_t)(0xffffffffu - (uint32_t)idx);
-    }
+    zxmlp::hidden32<1>(zxmlp::load_a(fb), p.wbf, p.param, s);
+    const float sc = zxmlp::sum_hidden(s, p.param[zxmlp::P_B2]);
+    const int idx = base + zxmlp::acc_row(lane & 15, lane);
+    if ((lane & 16) == 0 && idx < C)
+      p.key[idx] = ((uint64_t)float_order(sc) << 32) | (uint32_t)(0xffffffffu - (uint32_t)idx);
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
   }
