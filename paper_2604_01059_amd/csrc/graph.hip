@@ -250,6 +250,15 @@ __device__ __forceinline__ Ctx<LA> load_ctx(Shared& sh) {
   return c;
 }
 
+// A global pointer that all lanes agree on, in scalar registers, so that a
+// 32-bit lane offset is all the address a load needs.
+__device__ __forceinline__ __attribute__((address_space(1))) uint64_t* uniform_global(uint64_t* p) {
+  const uint64_t a = (uint64_t)p;
+  const uint64_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)a) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32;
+  return (__attribute__((address_space(1))) uint64_t*)u;
+}
+
 template <bool LA>
 __device__ __forceinline__ typename AdjPtr<LA>::type row_ptr(const Ctx<LA>& c, int r) {
   return c.adj + (size_t)r * c.ldw;
@@ -1036,7 +1045,147 @@ __device__ __noinline__ void apply_round_team(Shared& sh, bool pivot) {
   __syncthreads();
 }
 
-// Arena mode (rows in global memory), rounds of at most 64 rewrites.  Rows
+// Entries of group tables: 16 combinations of four contributions, `groups` of
+// them, W1 words an entry (odd), from spider s0 of the round.  A thread builds
+// the four entries of a word whose upper two bits are its own.  No barrier.
+template <int BS, bool LA>
+__device__ __forceinline__ void build_tables(const Ctx<LA>& c, LDSP uint64_t* tab, int W1, int s0, int ns, int groups) {
+  const int W = c.W;
+  for (int i = threadIdx.x; i < 4 * groups * W; i += BS) {
+    const int q4 = i / W, jj = i - q4 * W, g = q4 >> 2, up = q4 & 3;
+    uint64_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int s = s0 + 4 * g + q;
+      const uint64_t rv = row_ptr(c, c.slist[s < ns ? s : 0])[jj];
+      v[q] = s < ns ? rv : 0;
+    }
+    const uint64_t u = ((up & 1) ? v[2] : 0) ^ ((up & 2) ? v[3] : 0);
+    LDSP uint64_t* e = tab + (16 * g + 4 * up) * W1 + jj;
+    e[0] = u;
+    e[W1] = u ^ v[0];
+    e[2 * W1] = u ^ v[1];
+    e[3 * W1] = u ^ v[0] ^ v[1];
+  }
+}
+
+// The round update in arena mode (rows in global memory) for at most
+// SPIDER_MAJOR_MAX selected spiders, by contribution tables in the free LDS,
+// as apply_rows_lds does it: a wavefront owns a run of rows; one lane per row
+// for its hit mask and phase, then two words of a row per lane, three steps'
+// words loaded before the first is used.  An entry with one bit is a
+// contribution as it stands, so the hit bits come from the tables too (the
+// partner's entry for a pivot, whose rows were swapped).  Selected columns
+// are dropped in the same write.
+//
+// Bound: latency of the row words (L2).  1856 spiders, a round: 188 k cycles
+// with one dependent load, a 64-bit division and a walk over the hit bits per
+// word; now 63 k (1440 spiders: 119 k and 41 k; 1024 with the scoring areas in
+// LDS: 61 k and 23 k).  Not inlined, and three steps' words rather than eight
+// (which learned batches would take 4 % faster): more registers here raise
+// the kernel's above 128, and with a wavefront less per SIMD the LDS path
+// that shares it runs 25 % longer.
+__device__ __forceinline__ int arena_tab_words(int W, int groups) { return groups * 16 * (W + 2); }
+
+template <int BS, int GROUPS>
+__device__ __noinline__ void apply_rows_arena(Shared& sh, bool pivot) {
+  constexpr int NW = BS / 64, S = 4 * GROUPS, U = 3;
+  const Ctx<false> c = load_ctx<BS, false>(sh);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int W = c.W, n = c.n, ns = uni(sh.ns), ldw = uni(c.ldw);
+  __attribute__((address_space(1))) uint64_t* const rows_at = uniform_global(c.adj);
+  const int LW = (W + 1) / 2, W1 = 2 * LW | 1;
+  const int rpw = 64 / LW;  // W <= 128
+  const int rr = lane / LW, j = rr < rpw ? (lane - rr * LW) * 2 : 0;
+  const bool on = rr < rpw, two = j + 1 < W;
+  const int j1 = two ? j + 1 : j;
+  const int R = (n + NW - 1) / NW;
+  const int r0 = uni(wv * R), r1 = uni(r0 + R < n ? r0 + R : n);
+  const uint64_t keep0 = ~c.sel[j], keep1 = ~c.sel[j1];
+  // lane s: selected spider s, its phase increment, the place of the row that
+  // holds its neighbours in the round's list
+  const int xs = c.slist[lane < ns ? lane : 0];
+  const int kx = lane < ns ? c.kc[xs] : 0;
+  int ps = lane;
+  if (pivot) {
+    const int p = c.partner[xs];
+    for (int q = 0; q < ns; ++q) ps = __builtin_amdgcn_readlane(xs, q) == p ? q : ps;
+  }
+  int64_t pc = 0;
+  for (int s0 = 0; s0 < ns; s0 += S) {
+    const bool last = s0 + S >= ns;
+    const int sc = ns - s0 < S ? ns - s0 : S;
+    if (s0) __syncthreads();  // every wavefront is through with the tables
+    build_tables<BS, false>(c, c.scr, W1, s0, ns, GROUPS);
+    __syncthreads();
+    for (int base = r0; base < r1; base += 64) {
+      const int w = base + lane < n ? base + lane : n - 1;
+      const uint64_t live = c.alive[w >> 6] & ~c.sel[w >> 6];
+      const bool act = base + lane < r1 && ((live >> (w & 63)) & 1);
+      uint32_t hit = 0;
+      int dk = 0;
+      for (int q = 0; q < sc; ++q) {
+        const int s = s0 + q, pq = __builtin_amdgcn_readlane(ps, s);
+        // the neighbours' row of spider s: an entry of this pass, or the row itself
+        const bool here = pq >= s0 && pq < s0 + S;
+        const uint64_t nbw = here ? c.scr[(16 * ((pq - s0) >> 2) + (1 << ((pq - s0) & 3))) * W1 + (w >> 6)]
+                                  : row_ptr(c, __builtin_amdgcn_readlane(xs, pq))[w >> 6];
+        const uint32_t b = (uint32_t)(nbw >> (w & 63)) & 1u;
+        hit |= b << q;
+        dk += (int)b * __builtin_amdgcn_readlane(kx, s);
+        if (pivot) {  // adjacent to both ends: the spider's own row holds its partner's neighbours
+          const uint64_t own = c.scr[(16 * (q >> 2) + (1 << (q & 3))) * W1 + (w >> 6)];
+          dk += 2 * (int)(b & (uint32_t)(own >> (w & 63)));
+        }
+      }
+      if (act && (dk & 7)) c.k[w] = (int8_t)((c.k[w] + dk) & 7);
+      hit = act ? hit | 0x80000000u : 0;
+      const int rows = r1 - base < 64 ? r1 - base : 64;
+      for (int st = 0; st < rows; st += U * rpw) {
+        uint32_t hm[U];
+        uint64_t v0[U], v1[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int src = st + u * rpw + rr;
+          hm[u] = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * src, (int)hit);
+          const uint32_t at = (uint32_t)((src < rows ? base + src : base) * ldw);
+          v0[u] = rows_at[at + j];
+          v1[u] = rows_at[at + j1];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int src = st + u * rpw + rr, row = base + src;
+          uint64_t a = v0[u], b = v1[u];
+#pragma unroll
+          for (int g = 0; g < GROUPS; ++g) {
+            const LDSP uint64_t* e = c.scr + (int)(16 * g + __builtin_amdgcn_ubfe(hm[u], 4 * g, 4)) * W1 + j;
+            a ^= e[0];
+            b ^= e[1];
+          }
+          if (last) {
+            const uint32_t dg = 1u << (row & 31);
+            const uint64_t dm = (row & 32) ? (uint64_t)dg << 32 : dg;
+            a &= (j == (row >> 6) ? ~dm : ~0ull) & keep0;
+            b &= (j + 1 == (row >> 6) ? ~dm : ~0ull) & keep1;
+          }
+          if (on && src < rows && (hm[u] >> 31)) {
+            const uint32_t at = (uint32_t)(row * ldw) + j;
+            rows_at[at] = a;
+            if (two) rows_at[at + 1] = b;
+            if (last) pc += __popcll(a) + (two ? __popcll(b) : 0);
+          }
+        }
+      }
+    }
+  }
+  const int tot = __builtin_amdgcn_readlane(wave_sum_lane63((int)pc), 63);
+  if (lane == 0) block_add(&sh.acc64[3], tot);
+  __syncthreads();
+}
+
+// The same for rows of more than 128 words, which two words a lane do not
+// cover, and for budgets without room for tables.  Rows
 // go in chunks that fit the free LDS: a per-row pass records which selected
 // spiders the row is adjacent to (hit mask) and updates the row's phase;
 // then a (row, word) pass XORs the hit contributions, staged in LDS when
@@ -1217,23 +1366,7 @@ __device__ __forceinline__ void apply_rows_lds(Ctx<true>& c, Shared& sh, bool pi
     uint32_t lo[TAB ? 1 : APPLY_S], hi[TAB ? 1 : APPLY_S];
     if constexpr (TAB) {
       if (s0) __syncthreads();  // every wavefront is through with the tables
-      // thread: word jj of all entries whose upper two bits are its own
-      for (int i = threadIdx.x; i < APPLY_S * W; i += BS) {
-        const int q4 = i / W, jj = i - q4 * W, g = q4 >> 2, up = q4 & 3;
-        uint64_t v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int s = s0 + 4 * g + q;
-          const uint64_t rv = row_ptr(c, c.slist[s < ns ? s : 0])[jj];
-          v[q] = s < ns ? rv : 0;
-        }
-        const uint64_t u = ((up & 1) ? v[2] : 0) ^ ((up & 2) ? v[3] : 0);
-        LDSP uint64_t* e = c.scr + (16 * g + 4 * up) * W1 + jj;
-        e[0] = u;
-        e[W1] = u ^ v[0];
-        e[2 * W1] = u ^ v[1];
-        e[3 * W1] = u ^ v[0] ^ v[1];
-      }
+      build_tables<BS, true>(c, c.scr, W1, s0, ns, APPLY_S / 4);
       __syncthreads();
     } else {
 #pragma unroll
@@ -1369,7 +1502,18 @@ __device__ bool apply_round(Ctx<LA>& c, Shared& sh, bool pivot) {
         return true;
       }
     }
-    if (uni(sh.ns) <= SPIDER_MAJOR_MAX && c.scr_words >= 64) {
+    if (uni(sh.ns) <= SPIDER_MAJOR_MAX && c.W <= 128) {
+      // a second pass of tables reads the rows again: four groups where they are wanted and fit
+      if (uni(sh.ns) > 8 && c.scr_words >= arena_tab_words(c.W, 4)) {
+        apply_rows_arena<BS, 4>(sh, pivot);
+        return true;
+      }
+      if (c.scr_words >= arena_tab_words(c.W, 2)) {
+        apply_rows_arena<BS, 2>(sh, pivot);
+        return true;
+      }
+    }
+    if (uni(sh.ns) <= SPIDER_MAJOR_MAX && c.scr_words >= 64) {  // no room for tables, or more than two words a lane
       apply_round_arena<BS>(sh, pivot);
       return true;
     }

@@ -272,7 +272,7 @@ __device__ void pivot_features(Ctx<LA>& c, int u, int v, float invN, LDSP uint16
 // a few rounds a diagram's density is near one half and about log2(n) rows
 // reach everything; in a sparse one the neighbours are few.  (The product
 // A x A on the matrix cores does all n rows for all n spiders: scoring took
-// 60 k cycles a round at 640 spiders and 554 k at 1856; now @S6@ and @S18@.)
+// 60 k cycles a round at 640 spiders and 554 k at 1856; now 34 k and 107 k.)
 template <bool LA>
 __device__ void two_hop(Ctx<LA>& c, const LDSP uint32_t* list, int cnt, LDSP int32_t* th) {
   constexpr int Q = LA ? 4 : 8;  // rows in flight

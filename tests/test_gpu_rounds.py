@@ -75,3 +75,21 @@ def test_by_size_equals_one_variant(zx, count, q_hi):
         assert b.status() == zx.ZX_OK
         arenas.append(pool)
     assert torch.equal(arenas[0], arenas[2]) and torch.equal(arenas[1], arenas[2])
+
+
+@pytest.mark.parametrize("n,q,p", [(1153, 8, 0.002), (1280, 16, 0.1), (1409, 22, 0.003), (1472, 23, 0.02)])
+@pytest.mark.parametrize("pauli", [False, True])
+def test_arena_updates(zx, n, q, p, pauli):
+    """Rows that no LDS budget holds, of odd and even numbers of words, with
+    contribution tables of two and of four groups and one and several passes."""
+    d = diagram(72, n, q, p, pauli)
+    og = oracle.Graph.from_diagram(d)
+    assert og.simplify() == oracle.OK
+    for name in ("bs256-lds32k", "bs512-lds152k"):
+        print("arena updates", n, p, pauli, name, flush=True)
+        g = zx.Graph.from_diagram(d)
+        zx.simplify([g], tune_id=zx.simplify_variants().index(name))
+        adj, ph, al, info = g.read()
+        assert np.array_equal(al, og.alive) and np.array_equal(ph, og.k) and np.array_equal(adj, og.adj), name
+        assert info.fill_in == og.scalar.fill_in and info.phase8 == og.scalar.phase8 % 8
+        np.testing.assert_array_equal(g.trace(), og.trace)
