@@ -58,3 +58,24 @@ def test_invalid_model_sets_status(zx):
     torch.cuda.synchronize()
     assert S.status() == zx.ZX_EINVAL
     assert not zx.to_host_words(out).any()
+
+
+# chunks of one and of several shots a lane, ragged last ones; records in LDS
+# up to 4096 mechanisms; columns shorter and longer than a record's four bits;
+# gaps from certain (pmax = 1) to far beyond the model
+@pytest.mark.parametrize("n_err,n_f,pmax,n", [(50, 100, 0.02, 600001), (4096, 64, 2e-4, 1000), (4097, 65, 2e-4, 1000),
+                                              (64, 2048, 1.0, 130), (300, 10, 1e-12, 70000), (1, 1, 0.5, 530000)])
+def test_chunks_and_records(zx, n_err, n_f, pmax, n):
+    import torch
+    rng = np.random.default_rng(n_err + n_f)
+    cnt = rng.integers(0, 8, n_err)
+    ptr = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32)
+    idx = rng.integers(0, n_f, ptr[-1]).astype(np.int32)
+    prob = pmax * rng.random(n_err)
+    prob[0] = pmax
+    print("sample records", n_err, n_f, pmax, n, flush=True)
+    S = zx.DetectorSampler(ptr, idx, prob, n_f)
+    out = S.sample(31, 5, n)
+    torch.cuda.synchronize()
+    assert S.status() == 0
+    assert np.array_equal(zx.to_host_words(out), oracle.detector_sample(ptr, idx, prob, n_f, 31, 5, n))
