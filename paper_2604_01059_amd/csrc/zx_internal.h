@@ -177,6 +177,14 @@ struct ZxDevice {
 };
 const ZxDevice* zx_device();
 
+// Workgroups of bs threads and lds dynamic bytes that a CU holds: 8 wavefronts
+// a SIMD, 16 workgroups, its LDS with 1 KiB a workgroup for static data.
+inline int zx_groups_per_cu(const ZxDevice* d, size_t lds, int bs) {
+  const int by_lds = (int)(d->lds_per_block / (lds + 1024)), by_waves = 32 / (bs / 64);
+  const int g = by_lds < by_waves ? by_lds : by_waves;
+  return g < 1 ? 1 : (g > 16 ? 16 : g);
+}
+
 zx_status zx_pauli_commute_mfma(const uint64_t* X, const uint64_t* Z, int64_t n, int32_t n_qubits, int64_t ldq,
                                 uint64_t* C, int64_t ldc, hipStream_t s);
 

@@ -115,3 +115,14 @@ def test_capacity(zx):
     g = zx.Graph.from_diagram(serve_diagram(5, i))
     with pytest.raises(zx.ZxError):
         zx.extract([g])
+
+
+# words a row holds: 2, 4, 5, 6, 7, 9, 5 and 6 (65 rows)
+@pytest.mark.parametrize("q,depth", [(14, 6), (20, 40), (63, 3), (30, 60), (64, 40), (64, 80), (65, 3), (65, 20)])
+def test_elimination_forms(zx, q, depth):
+    """Frontiers and row widths on both sides of one wavefront's registers
+    (64 rows, 4 and 8 words), before simplification (many rounds) and after."""
+    ds = [circuit_workload(9, i, q_lo=q, q_hi=q, d_lo=depth, d_hi=depth) for i in range(3)]
+    print("elimination forms", q, depth, [(d.n + 2 * len(d.inputs) + 63) // 64 for d in ds], flush=True)
+    assert check(zx, ds, False) == len(ds)
+    assert check(zx, ds, True) == len(ds)
