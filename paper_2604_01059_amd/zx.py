@@ -673,17 +673,18 @@ def gflow(graphs, stream=None):
     import torch
     n = len(graphs)
     total = sum(g.n for g in graphs)
-    layers = torch.empty(max(total, 1), dtype=torch.int32, device="cuda")
-    exists = torch.empty(n, dtype=torch.int32, device="cuda")
+    res = torch.empty(n + max(total, 1), dtype=torch.int32, device="cuda")  # one copy back
+    exists, layers = res[:n], res[n:]
     nb = load().zx_gflow_workspace_bytes(n)
     ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
     _check(load().zx_gflow(_graph_array(graphs), n, _ptr(layers), _ptr(exists), _ptr(ws), nb, _stream(stream)))
-    lay = layers.cpu().numpy()
+    res = res.cpu().numpy()
+    lay = res[n:]
     out, off = [], 0
     for g in graphs:
         out.append(lay[off:off + g.n].copy())
         off += g.n
-    return exists.cpu().numpy(), out
+    return res[:n].copy(), out
 
 
 def decode_gates(words):
@@ -712,18 +713,20 @@ def extract(graphs, max_gates=None, stream=None, raw=False):
     if max_gates is None:
         max_gates = max(64, max((g.n + 2 * g.n_in) * (g.n_out + 4) for g in graphs))
     gates = torch.empty(n * max_gates, dtype=torch.int32, device="cuda")
-    n_gates = torch.empty(n, dtype=torch.int32, device="cuda")
-    perm = torch.empty(max(1, sum(g.n_out for g in graphs)), dtype=torch.int32, device="cuda")
-    status = torch.empty(n, dtype=torch.int32, device="cuda")
+    res = torch.empty(2 * n + max(1, sum(g.n_out for g in graphs)), dtype=torch.int32, device="cuda")
+    n_gates, status, perm = res[:n], res[n:2 * n], res[2 * n:]
     nb = load().zx_extract_workspace_bytes(n)
     ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
     _check(load().zx_extract(_graph_array(graphs), n, int(max_gates), _ptr(gates), _ptr(n_gates), _ptr(perm),
                              _ptr(status), _ptr(ws), nb, _stream(stream)))
-    G = gates.cpu().numpy().view(np.uint32).reshape(n, max_gates)
-    ng, st, pm = n_gates.cpu().numpy(), status.cpu().numpy(), perm.cpu().numpy()
+    res = res.cpu().numpy()
+    ng, st, pm = res[:n], res[n:2 * n], res[2 * n:]
     need = int(ng[st == ZX_ECAPACITY].max()) if (st == ZX_ECAPACITY).any() else 0
     if need > max_gates:  # the buffer was short: once more with the counted size
         return extract(graphs, max_gates=need, stream=stream, raw=raw)
+    # only as many columns as the longest list: the bound is several times what is emitted
+    used = min(int(ng.max(initial=0)), max_gates)
+    G = gates.view(n, max_gates)[:, :used].contiguous().cpu().numpy().view(np.uint32)
     out, off = [], 0
     for i, g in enumerate(graphs):
         words = G[i, :min(int(ng[i]), max_gates)].copy()
