@@ -272,41 +272,54 @@ __device__ void pivot_features(Ctx<LA>& c, int u, int v, float invN, LDSP uint16
 // a few rounds a diagram's density is near one half and about log2(n) rows
 // reach everything; in a sparse one the neighbours are few.  (The product
 // A x A on the matrix cores does all n rows for all n spiders: scoring took
-// 60 k cycles a round at 640 spiders and 554 k at 1856; now 34 k and 107 k.)
-template <bool LA>
-__device__ void two_hop(Ctx<LA>& c, const LDSP uint32_t* list, int cnt, LDSP int32_t* th) {
-  constexpr int Q = LA ? 4 : 8;  // rows in flight
+// 60 k cycles a round at 640 spiders and 554 k at 1856; 34 k and 107 k with one
+// candidate a lane and whole blocks of 32, now 17 k and 72 k.)
+//
+// A lane has two words in hand: of one candidate in rows of more than 64
+// words (PAIR false), else the same word of two candidates, so that twice as
+// many rows are in flight.
+template <bool LA, bool PAIR>
+__device__ __forceinline__ void two_hop_words(Ctx<LA>& c, const LDSP uint32_t* list, int cnt, LDSP int32_t* th) {
+  constexpr int Q = LA ? 4 : 8;  // rows in flight per candidate
   const int lane = threadIdx.x & 63, W = c.W;
   int Wp = 1;
   while (Wp < W && Wp < 64) Wp <<= 1;
   const int G = 64 / Wp, g = lane / Wp, j = lane & (Wp - 1);
-  const bool in0 = j < W, in1 = j + 64 < W;
-  const int j0 = in0 ? j : W - 1, j1 = in1 ? j + 64 : W - 1;
-  for (int b = 0; b < cnt; b += G) {
-    const bool has = b + g < cnt;
-    const int x = (int)list[has ? b + g : b];
-    const auto rx = row_ptr(c, x);
-    const uint64_t me = 1ull << (x & 63);
-    uint64_t l0 = has && in0 ? c.alive[j0] & ~rx[j0] & ~((x >> 6) == j0 ? me : 0) : 0;
-    uint64_t l1 = has && in1 ? c.alive[j1] & ~rx[j1] & ~((x >> 6) == j1 ? me : 0) : 0;
-    const int total = __popcll(l0) + __popcll(l1);
-    uint64_t next = rx[0];
+  const bool in0 = j < W, in1 = PAIR ? in0 : j + 64 < W;
+  const int j0 = in0 ? j : W - 1, j1 = PAIR ? j0 : in1 ? j + 64 : W - 1;
+  for (int b = 0; b < cnt; b += PAIR ? 2 * G : G) {
+    const int e0 = b + g, e1 = PAIR ? b + G + g : e0;
+    const bool has0 = e0 < cnt, has1 = e1 < cnt;
+    const int x0 = (int)list[has0 ? e0 : b], x1 = PAIR ? (int)list[has1 ? e1 : b] : x0;
+    const auto r0 = row_ptr(c, x0), r1 = row_ptr(c, x1);
+    const uint64_t m0 = 1ull << (x0 & 63), m1 = 1ull << (x1 & 63);
+    uint64_t n0 = r0[0], n1 = PAIR ? r1[0] : 0;
+    const uint64_t a0 = r0[j0], a1 = r1[j1];
+    uint64_t l0 = has0 && in0 ? c.alive[j0] & ~a0 & ~((x0 >> 6) == j0 ? m0 : 0) : 0;
+    uint64_t l1 = has1 && in1 ? c.alive[j1] & ~a1 & ~((x1 >> 6) == j1 ? m1 : 0) : 0;
+    const int t0 = __popcll(l0), t1 = __popcll(l1);
     for (int w = 0; w < W; ++w) {
-      const uint64_t cur = has ? next : 0;
-      next = rx[w + 1 < W ? w + 1 : w];
+      const uint64_t c0 = has0 ? n0 : 0, c1 = PAIR && has1 ? n1 : 0;
+      n0 = r0[w + 1 < W ? w + 1 : w];
+      if (PAIR) n1 = r1[w + 1 < W ? w + 1 : w];
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
-        uint32_t d = (uint32_t)(cur >> (32 * half));
-        while (__ballot(d != 0)) {
+        uint32_t d0 = (uint32_t)(c0 >> (32 * half)), d1 = (uint32_t)(c1 >> (32 * half));
+        while (__ballot((d0 | d1) != 0)) {
           uint64_t v0[Q], v1[Q];
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
-            // a group that is through reads its own row, whose spiders are out already
-            const int u = d ? 64 * w + 32 * half + __builtin_ctz(d) : x;
-            const auto ru = row_ptr(c, u);
-            v0[q] = ru[j0];
-            v1[q] = W > 64 ? ru[j1] : 0;
-            d &= d - 1;
+            // a candidate that is through reads its own row, whose spiders are out already
+            const int u0 = d0 ? 64 * w + 32 * half + __builtin_ctz(d0) : x0;
+            v0[q] = row_ptr(c, u0)[j0];
+            d0 &= d0 - 1;
+            if (PAIR) {
+              const int u1 = d1 ? 64 * w + 32 * half + __builtin_ctz(d1) : x1;
+              v1[q] = row_ptr(c, u1)[j1];
+              d1 &= d1 - 1;
+            } else {
+              v1[q] = row_ptr(c, u0)[j1];
+            }
           }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -319,10 +332,21 @@ __device__ void two_hop(Ctx<LA>& c, const LDSP uint32_t* list, int cnt, LDSP int
       }
       if (!__ballot((l0 | l1) != 0)) break;
     }
-    int k = total - __popcll(l0) - __popcll(l1);
-    for (int o = 1; o < Wp; o <<= 1) k += __shfl_xor(k, o);
-    if (has && j == 0) th[b + g] = k;
+    int k0 = t0 - __popcll(l0), k1 = t1 - __popcll(l1);
+    if (!PAIR) k0 += k1;
+    for (int o = 1; o < Wp; o <<= 1) {
+      k0 += __shfl_xor(k0, o);
+      if (PAIR) k1 += __shfl_xor(k1, o);
+    }
+    if (has0 && j == 0) th[e0] = k0;
+    if (PAIR && has1 && j == 0) th[e1] = k1;
   }
+}
+
+template <bool LA>
+__device__ __forceinline__ void two_hop(Ctx<LA>& c, const LDSP uint32_t* list, int cnt, LDSP int32_t* th) {
+  if (c.W <= 64) two_hop_words<LA, true>(c, list, cnt, th);
+  else two_hop_words<LA, false>(c, list, cnt, th);
 }
 
 // Features of a block of up to 32 candidates (list entries base..base+cnt)
@@ -393,8 +417,15 @@ __device__ void policy_score(Ctx<LA>& c, Pol& p, int C, float invN, bool pivot) 
   LDSP uint16_t* fb = p.fbuf + wv * 32 * zxmlp::IN;
   LDSP int32_t* tb = p.thbuf + wv * 64;
   LDSP uint32_t* el = p.elist + wv * 64;
-  for (int base = wv * 32; base < C; base += (BS / 64) * 32) {
-    const int cnt = C - base < 32 ? C - base : 32;
+  // blocks of up to 32, as even as the wavefronts' shares can be: of 33
+  // candidates per wavefront none has to wait for a second block of 32
+  constexpr int NW = BS / 64;
+  const int each = (C + NW - 1) / NW, turns = (each + 31) / 32;
+  const int size = turns ? (each + turns - 1) / turns : 0;
+  for (int turn = 0; turn < turns; ++turn) {
+    const int base = (turn * NW + wv) * size;
+    if (base >= C) break;
+    const int cnt = C - base < size ? C - base : size;
     if (pivot) {
       const int r = lane & 31;
       const uint32_t e = r < cnt ? p.list[base + r] : 0u;
@@ -415,7 +446,7 @@ __device__ void policy_score(Ctx<LA>& c, Pol& p, int C, float invN, bool pivot) 
     zxmlp::hidden32<1>(zxmlp::load_a(fb), p.wbf, p.param, s);
     const float sc = zxmlp::sum_hidden(s, p.param[zxmlp::P_B2]);
     const int idx = base + zxmlp::acc_row(lane & 15, lane);
-    if ((lane & 16) == 0 && idx < C)
+    if ((lane & 16) == 0 && idx < base + cnt)
       p.key[idx] = ((uint64_t)float_order(sc) << 32) | (uint32_t)(0xffffffffu - (uint32_t)idx);
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();

@@ -499,3 +499,30 @@ def test_mlp_backward_parts(zx, rows):
     W1, b1, w2, b2 = omlp.unpack(p)
     mag = np.abs(ref).max() + np.abs(d).sum() * 8.0
     assert np.abs(g - ref).max() <= 8 * np.sqrt(rows + 64.0) * 2.0 ** -24 * mag
+
+
+@pytest.mark.parametrize("n,q,density", [(70, 4, 0.1), (130, 4, 0.04), (640, 8, 0.004), (1030, 8, 0.003),
+                                         (1857, 8, 0.004), (4101, 8, 0.0008)])
+def test_first_round_by_two_hop_counts(zx, n, q, density):
+    """A network that passes the two-hop feature through (one hidden unit, all
+    else zero: bf16 in, exact products and sums) orders the first round by the
+    counts alone, ties by index: rows of 2 to 65 words, so two candidates a
+    lane and one; candidate counts that do not divide among the wavefronts."""
+    from workloads import make_diagram
+    d = make_diagram(91, n, q, n, density)
+    p = np.zeros(omlp.NPARAM, np.float32)
+    W1, b1, w2, b2 = omlp.unpack(p)
+    W1[5, 0] = 1.0
+    w2[0] = 1.0
+    assert p.sum() == 2.0  # the views write through
+    g0 = oracle.Graph.from_diagram(d)
+    ent = opol.candidate_list(g0)
+    s, _ = omlp.forward(p, np.stack([opol.features(g0, u) for u, _ in ent]))
+    assert len(np.unique(s)) > 1
+    taken = []
+    for j in sorted(range(len(ent)), key=lambda j: (-s[j], j)):
+        if not any(g0.edge(ent[j][0], t) for t in taken):
+            taken.append(ent[j][0])
+    print("two-hop order", n, len(ent), len(taken), flush=True)
+    tr = learned_run(zx, [d], p, max_rounds=1)[0].trace()
+    assert sorted(int(u) for u in tr[:, 2]) == sorted(taken)
