@@ -3321,9 +3321,12 @@ static std::vector<Segment> plan_segments(const std::vector<int32_t>& sizes, int
   // each takes longer (1.7 and 2.5 times, fits of the times below), but more
   // run at a time.  Diagrams of 16 to 1024 spiders, by-size runs against one
   // launch: 4096 of them 2.75 and 2.13 ms, 2048 1.78 and 1.34, 1024 1.00
-  // and 1.15, 4096 of up to 512 0.92 and 0.63.
+  // and 1.15, 4096 of up to 512 0.92 and 0.63.  Only budgets that hold the
+  // largest diagram's auxiliary arrays (32 KiB: to 4672 spiders): the kernel
+  // refuses a diagram otherwise.
   const double arena[3] = {0.0, 1.7, 2.5};
   for (int k = 1; k < 3; ++k) {
+    if (begin < n && aux_bytes(sizes[begin], (sizes[begin] + 63) / 64) > kVariants[budgets[k].variant].lds_cap) continue;
     double total = 0, longest = 0;
     for (int32_t i = begin; i < n; ++i) {
       const double c = alone(sizes[i]) * (i < first[k] ? arena[k] : budgets[k].slow);
@@ -3339,6 +3342,19 @@ static std::vector<Segment> plan_segments(const std::vector<int32_t>& sizes, int
   return best;
 }
 
+// The plan of a greedy batch without a variant asked for, for the host tests:
+// sizes descending, launches of the diagrams begin .. n - 1 (at most three).
+extern "C" int32_t zx_plan_launches(const int32_t* sizes, int32_t n, int32_t begin, int32_t n_cu, int32_t* variant,
+                                    int32_t* first, int32_t* count) {
+  const std::vector<Segment> segs = plan_segments(std::vector<int32_t>(sizes, sizes + n), begin, n_cu);
+  for (size_t i = 0; i < segs.size(); ++i) {
+    variant[i] = segs[i].variant;
+    first[i] = segs[i].begin;
+    count[i] = segs[i].count;
+  }
+  return (int32_t)segs.size();
+}
+
 struct zx_batch {
   uint8_t** table_dev;  // in the workspace
   Queue* queue;         // in the workspace
@@ -3352,7 +3368,15 @@ struct zx_batch {
   std::vector<Segment> segments;  // the by-size launches of the others
 };
 
+static bool variant_fits_n(int max_n, int v, bool learned);
+
 static zx_status launch_segments(const zx_batch* b, const std::vector<Segment>& segs, const SimpArgs& a, hipStream_t s) {
+  // the device would refuse the diagram in its header alone
+  for (const Segment& g : segs)
+    if (!variant_fits_n(b->sizes[g.begin], g.variant, false)) {
+      zx_set_error("diagrams too large for simplify variant %d", g.variant);
+      return ZX_ECAPACITY;
+    }
   for (const Segment& g : segs) {
     const zx_status st = launch_simplify(g.variant, b->table_dev + g.begin, g.count, b->queue, a, false, s);
     if (st != ZX_OK) return st;

@@ -93,3 +93,22 @@ def test_arena_updates(zx, n, q, p, pauli):
         assert np.array_equal(al, og.alive) and np.array_equal(ph, og.k) and np.array_equal(adj, og.adj), name
         assert info.fill_in == og.scalar.fill_in and info.phase8 == og.scalar.phase8 % 8
         np.testing.assert_array_equal(g.trace(), og.trace)
+
+
+def test_many_large_diagrams(zx):
+    """More large diagrams than a CU holds workgroups for, of a size whose
+    auxiliary arrays exceed the smallest LDS budget: the default plan runs
+    every one (a budget they do not fit leaves them as they were)."""
+    import torch
+    n, count = 4700, 800
+    d = make_diagram(83, n, 4, n, 0.0008)
+    one = zx.Graph.from_diagram(d)
+    pool = one.arena[None, :].repeat(count, 1)
+    gs = [zx.Graph.attach(pool[i]) for i in range(count)]
+    print("many large", n, count, flush=True)
+    zx.simplify([one], tune_id=zx.simplify_variants().index("bs512-lds152k"), max_rounds=3, extract=False)
+    assert one.info().n_trace > 0
+    b = zx.Batch(gs)
+    b.run(max_rounds=3, extract=False)
+    assert b.status() == zx.ZX_OK
+    assert bool((pool == one.arena[None, :]).all())
