@@ -3576,7 +3576,9 @@ extern "C" zx_status zx_batch_simplify(zx_batch* b, const zx_simplify_opts* o, h
   // with the fallback, diagrams beyond the learned policy's LDS budget run greedy
   if (fb && !variant_fits(b, v, true) && o->tune_id < 0) {
     v = pick_variant(b, o->tune_id, false);
-    if (kVariants[v].bs < 256) {  // the learned kernel does not come in one wavefront
+    // the learned kernel comes neither in one wavefront nor by size; its LDS
+    // budget decides which diagrams compare both schedules
+    if (kVariants[v].bs < 256 || v == kBySizeVariant) {
       const int w = pick_variant_n(b->max_n, false);
       v = w >= 0 ? w : kDefaultVariant;
     }

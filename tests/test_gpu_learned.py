@@ -9,7 +9,7 @@ import torch
 import oracle
 from oracle import mlp as omlp
 from oracle import policy as opol
-from workloads import batch_diagram, single_diagram
+from workloads import batch_diagram, make_diagram, single_diagram
 
 pytestmark = pytest.mark.gpu
 
@@ -526,3 +526,22 @@ def test_first_round_by_two_hop_counts(zx, n, q, density):
     print("two-hop order", n, len(ent), len(taken), flush=True)
     tr = learned_run(zx, [d], p, max_rounds=1)[0].trace()
     assert sorted(int(u) for u in tr[:, 2]) == sorted(taken)
+
+
+def test_fallback_beside_a_diagram_beyond_the_learned_budget(zx):
+    """Beside a diagram that no learned budget holds, the fallback compares
+    both schedules up to 2048 spiders (the 64 KiB budget) and runs the others
+    greedily.  Phases of pi/4 leave nothing to rewrite, so both schedules
+    cost the same and the learned one is kept wherever it was compared."""
+    m = make_mlp(zx, rand_param(np.random.default_rng(29)))
+    sizes = [1000, 2048, 2112, 6500, 7400]
+    gs = []
+    for n in sizes:
+        d = make_diagram(92, n, 4, n, 3.0 / n)
+        gs.append(zx.Graph.create(d.adj, np.ones(n, np.int8), d.inputs, d.outputs, d.bnd_is_h))
+    print("fallback budget", sizes, flush=True)
+    zx.simplify(gs, policy=zx.ZX_POLICY_LEARNED, mlp=m, fallback=True)
+    info = [g.info() for g in gs]
+    assert all(i.status == 0 and i.n_trace == 0 and i.rank >= 0 for i in info)
+    L, G = zx.ZX_POLICY_LEARNED, zx.ZX_POLICY_GREEDY
+    assert [i.policy for i in info] == [L, L, G, G, G]
