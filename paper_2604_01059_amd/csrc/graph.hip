@@ -3274,26 +3274,35 @@ static int64_t lds_need(int n) {
 // this model: a launch lasts as long as its largest diagram, or its diagrams'
 // times spread over the resident workgroups.  Times of one diagram alone
 // (us, measured 128 spiders: 83, 256: 150, 512: 332, 1024: 877; arena mode
-// 1440: 6400), longer by 5 % and 25 % with two and four on a CU.  4096
-// diagrams of 4-64 qubits: 3.9 ms with 152 KiB for all, 3.0 with 64 KiB, 2.7
-// in three launches; of 4-24 qubits: 1.4, 0.79, 0.47 with 32 KiB.
+// 1472: 3000, 3000: 24000, 4600: 100000), longer by 5 % and 25 % with two and
+// four on a CU.  4096 diagrams of 4-64 qubits: 3.9 ms with 152 KiB for all,
+// 3.0 with 64 KiB, 2.7 in three launches; of 4-24 qubits: 1.4, 0.79, 0.47
+// with 32 KiB.
 static std::vector<Segment> plan_segments(const std::vector<int32_t>& sizes, int32_t begin, int n_cu) {
   const int32_t n = (int32_t)sizes.size();
   struct Budget { int variant, per_cu; double slow; };
   const Budget budgets[3] = {{5, 1, 1.0}, {4, 2, 1.05}, {0, 4, 1.25}};
   auto alone = [](int m) {
     const double x = m / 1000.0;
-    return lds_need(m) <= kVariants[5].lds_cap ? m * (0.55 + 0.3 * x) : 2230.0 * x * x * x;
+    return lds_need(m) <= kVariants[5].lds_cap ? m * (0.55 + 0.3 * x) : 940.0 * x * x * x;
   };
-  // first diagram of the sorted run that a budget takes in LDS
-  int32_t first[3];
-  for (int k = 0; k < 3; ++k) {
-    first[k] = begin;
-    if (k > 0)
-      while (first[k] < n && lds_need(sizes[first[k]]) > kVariants[budgets[k].variant].lds_cap) ++first[k];
-  }
+  // first diagram of the sorted run that a budget takes in LDS; the largest
+  // budget also runs those before `held`, which none does
+  auto in_lds = [&](int k) {
+    int32_t i = begin;
+    while (i < n && lds_need(sizes[i]) > kVariants[budgets[k].variant].lds_cap) ++i;
+    return i;
+  };
+  const int32_t held = in_lds(0), first[3] = {begin, in_lds(1), in_lds(2)};
   std::vector<double> sum((size_t)(n - begin) + 1, 0.0);
   for (int32_t i = begin; i < n; ++i) sum[i - begin + 1] = sum[i - begin] + alone(sizes[i]);
+  // Diagrams that no budget holds are long and few: of more than r slots of
+  // them, a workgroup runs r + 1.
+  auto rounds = [&](int64_t slots) {
+    double t = 0;
+    for (int64_t r = 1; begin + r * slots < held; ++r) t = std::max(t, (double)(r + 1) * alone(sizes[begin + r * slots]));
+    return t;
+  };
   std::vector<Segment> best;
   double best_t = 1e300;
   for (int use = 1; use < 8; ++use) {  // budgets used, as bits
@@ -3308,7 +3317,8 @@ static std::vector<Segment> plan_segments(const std::vector<int32_t>& sizes, int
       ok = ok && b >= first[k];
       if (b < end) {
         seg.insert(seg.begin(), Segment{budgets[k].variant, b, end - b});
-        t += budgets[k].slow * std::max(alone(sizes[b]), (sum[end - begin] - sum[b - begin]) / (n_cu * budgets[k].per_cu)) + 5.0;
+        t += budgets[k].slow * std::max({alone(sizes[b]), (sum[end - begin] - sum[b - begin]) / (n_cu * budgets[k].per_cu),
+                                         b < held ? rounds(n_cu * budgets[k].per_cu) : 0.0}) + 5.0;
       }
       end = b;
     }
@@ -3323,17 +3333,21 @@ static std::vector<Segment> plan_segments(const std::vector<int32_t>& sizes, int
   // launch: 4096 of them 2.75 and 2.13 ms, 2048 1.78 and 1.34, 1024 1.00
   // and 1.15, 4096 of up to 512 0.92 and 0.63.  Only budgets that hold the
   // largest diagram's auxiliary arrays (32 KiB: to 4672 spiders): the kernel
-  // refuses a diagram otherwise.
-  const double arena[3] = {0.0, 1.7, 2.5};
+  // refuses a diagram otherwise.  Diagrams that no budget holds in LDS take
+  // 1.45 times as long two on a CU, and up to 4.2 times four on a CU with half
+  // the threads: 300 of 1472 spiders 3.8 ms with 64 KiB, 5.9 with 152 and 5.5
+  // with 32, 1024 of them 9.2, 12.3 and 12.7; of 4600, 300 sparse ones 84, 115
+  // and 144.
+  const double arena[3] = {0.0, 1.7, 2.5}, none[3] = {0.0, 1.45, 4.2};
   for (int k = 1; k < 3; ++k) {
     if (begin < n && aux_bytes(sizes[begin], (sizes[begin] + 63) / 64) > kVariants[budgets[k].variant].lds_cap) continue;
     double total = 0, longest = 0;
     for (int32_t i = begin; i < n; ++i) {
-      const double c = alone(sizes[i]) * (i < first[k] ? arena[k] : budgets[k].slow);
+      const double c = alone(sizes[i]) * (i < held ? none[k] : i < first[k] ? arena[k] : budgets[k].slow);
       total += c;
       longest = std::max(longest, c);
     }
-    const double t = std::max(longest, total / (n_cu * budgets[k].per_cu)) + 5.0;
+    const double t = std::max({longest, total / (n_cu * budgets[k].per_cu), none[k] * rounds(n_cu * budgets[k].per_cu)}) + 5.0;
     if (t < best_t && begin < n) {
       best_t = t;
       best.assign(1, Segment{budgets[k].variant, begin, n - begin});

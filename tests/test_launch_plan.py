@@ -64,3 +64,11 @@ def test_uneven_sizes_fit(lib):
         sizes.sort(reverse=True)
         begin = rng.choice([0, 0, 1, min(8, len(sizes)), len(sizes)])
         check(lib, sizes, begin)
+
+
+@pytest.mark.parametrize("n", [1153, 1472, 2048, 3000, 4600, 6500, 8192])
+@pytest.mark.parametrize("count", [257, 300, 512, 600, 1024, 4096])
+def test_rows_that_no_budget_holds(lib, n, count):
+    """Diagrams whose rows no budget holds, more of them than CUs: two on a CU
+    (64 KiB) take less time than one (152 KiB) or four with half the threads."""
+    assert [budget(lib, v) for v, _, _ in plan(lib, [n] * count)] == [64 * 1024]
