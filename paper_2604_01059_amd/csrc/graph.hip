@@ -1085,9 +1085,17 @@ __device__ __forceinline__ void build_tables(const Ctx<LA>& c, LDSP uint64_t* ta
 // (which learned batches would take 4 % faster): more registers here raise
 // the kernel's above 128, and with a wavefront less per SIMD the LDS path
 // that shares it runs 25 % longer.
+//
+// Rows that are gone or selected read one row in place of their own: half of
+// the bytes late in a run (3000 spiders of degree 40, 600 of them: 69.6 ->
+// 63.6 ms).  SKIP: rows without a hit are not written.  Many sparse diagrams
+// at a time are bound by these bytes (4600 spiders of degree 3, 300 of them:
+// 82.6 -> 79.9 ms); up to ARENA_SKIP_W words a row the branch costs dense ones
+// more (64 of 1280 to 1472 spiders: 2.45 -> 2.50 ms).
+constexpr int ARENA_SKIP_W = 32;
 __device__ __forceinline__ int arena_tab_words(int W, int groups) { return groups * 16 * (W + 2); }
 
-template <int BS, int GROUPS>
+template <int BS, int GROUPS, bool SKIP>
 __device__ __noinline__ void apply_rows_arena(Shared& sh, bool pivot) {
   constexpr int NW = BS / 64, S = 4 * GROUPS, U = 3;
   const Ctx<false> c = load_ctx<BS, false>(sh);
@@ -1139,7 +1147,9 @@ __device__ __noinline__ void apply_rows_arena(Shared& sh, bool pivot) {
         }
       }
       if (act && (dk & 7)) c.k[w] = (int8_t)((c.k[w] + dk) & 7);
-      hit = act ? hit | 0x80000000u : 0;
+      // bit 31: a row to count; bit 30: one that changes (selected columns are
+      // set in rows with a hit, of this pass or of an earlier one)
+      hit = act ? hit | (!SKIP || hit || (last && s0) ? 0xC0000000u : 0x80000000u) : 0;
       const int rows = r1 - base < 64 ? r1 - base : 64;
       for (int st = 0; st < rows; st += U * rpw) {
         uint32_t hm[U];
@@ -1148,7 +1158,8 @@ __device__ __noinline__ void apply_rows_arena(Shared& sh, bool pivot) {
         for (int u = 0; u < U; ++u) {
           const int src = st + u * rpw + rr;
           hm[u] = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * src, (int)hit);
-          const uint32_t at = (uint32_t)((src < rows ? base + src : base) * ldw);
+          const bool go = src < rows && (hm[u] >> 31);  // else the same row for all
+          const uint32_t at = (uint32_t)((go ? base + src : base) * ldw);
           v0[u] = rows_at[at + j];
           v1[u] = rows_at[at + j1];
         }
@@ -1171,8 +1182,10 @@ __device__ __noinline__ void apply_rows_arena(Shared& sh, bool pivot) {
           }
           if (on && src < rows && (hm[u] >> 31)) {
             const uint32_t at = (uint32_t)(row * ldw) + j;
-            rows_at[at] = a;
-            if (two) rows_at[at + 1] = b;
+            if (!SKIP || (hm[u] >> 30 & 1)) {
+              rows_at[at] = a;
+              if (two) rows_at[at + 1] = b;
+            }
             if (last) pc += __popcll(a) + (two ? __popcll(b) : 0);
           }
         }
@@ -1505,11 +1518,13 @@ __device__ bool apply_round(Ctx<LA>& c, Shared& sh, bool pivot) {
     if (uni(sh.ns) <= SPIDER_MAJOR_MAX && c.W <= 128) {
       // a second pass of tables reads the rows again: four groups where they are wanted and fit
       if (uni(sh.ns) > 8 && c.scr_words >= arena_tab_words(c.W, 4)) {
-        apply_rows_arena<BS, 4>(sh, pivot);
+        if (c.W > ARENA_SKIP_W) apply_rows_arena<BS, 4, true>(sh, pivot);
+        else apply_rows_arena<BS, 4, false>(sh, pivot);
         return true;
       }
       if (c.scr_words >= arena_tab_words(c.W, 2)) {
-        apply_rows_arena<BS, 2>(sh, pivot);
+        if (c.W > ARENA_SKIP_W) apply_rows_arena<BS, 2, true>(sh, pivot);
+        else apply_rows_arena<BS, 2, false>(sh, pivot);
         return true;
       }
     }

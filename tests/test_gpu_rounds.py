@@ -112,3 +112,24 @@ def test_many_large_diagrams(zx):
     b.run(max_rounds=3, extract=False)
     assert b.status() == zx.ZX_OK
     assert bool((pool == one.arena[None, :]).all())
+
+
+@pytest.mark.parametrize("n,q,p", [(2048, 8, 0.003), (2049, 8, 0.05), (2177, 16, 0.0015), (3009, 8, 0.001)])
+@pytest.mark.parametrize("pauli", [False, True])
+def test_arena_updates_of_wide_rows(zx, n, q, p, pauli):
+    """Rows on both sides of 32 words, beyond which rows without a hit are not
+    written: sparse rounds of one and of several passes of tables, in which
+    most rows have none, and dense ones."""
+    d = diagram(73, n, q, p, pauli)
+    og = oracle.Graph.from_diagram(d)
+    assert og.simplify() == oracle.OK
+    for name in ("bs256-lds32k", "bs512-lds64k", "bs512-lds152k"):
+        print("arena wide", n, p, pauli, name, flush=True)
+        g = [zx.Graph.from_diagram(d)]
+        g += [g[0].snapshot() for _ in range(11)]  # so many that no team takes them
+        zx.simplify(g, tune_id=zx.simplify_variants().index(name))
+        for x in (g[0], g[11]):
+            adj, ph, al, info = x.read()
+            assert np.array_equal(al, og.alive) and np.array_equal(ph, og.k) and np.array_equal(adj, og.adj), name
+            assert info.fill_in == og.scalar.fill_in and info.phase8 == og.scalar.phase8 % 8
+            np.testing.assert_array_equal(x.trace(), og.trace)
