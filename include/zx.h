@@ -324,7 +324,7 @@ zx_status zx_gf2_profile_read(const void* ws, int32_t m, int64_t* ticks, int32_t
  * Variants: ZX_PAULI_FORCE_VALU, bitwise AND/XOR on the vector units;
  * ZX_PAULI_FORCE_MFMA, the same product on the matrix cores (bits as FP4
  * values, exact fp32 counts, see zx_gf2_matmul).  ZX_PAULI_AUTO takes the
- * matrix cores (below 2^22 qubits).  Both give identical bits.
+ * matrix cores.  Both give identical bits.
  * ==================================================================== */
 #define ZX_PAULI_AUTO 0u
 #define ZX_PAULI_FORCE_VALU 0x1u

@@ -9,9 +9,9 @@
 //    channels" for the encoding).  The paper contracts in floating point on
 //    BLAS; here the bits enter v_mfma_scale_f32_32x32x64_f8f6f4 as FP4
 //    (E2M1) values: a set bit is the code 0b0001 (0.5), the block scale 2^1
-//    makes it 1.0, so every product is 0 or 1 and the fp32 sums (at most the
-//    row length, far below 2^24) are exact counts; bit 0 of the count is the
-//    parity.  Bits are unpacked by bit plane: plane t of four consecutive
+//    makes it 1.0, so every product is 0 or 1 and the fp32 sums (of at most
+//    2^22 bits: longer rows go in parts, a launch each) are exact counts; bit
+//    0 of the count is the parity.  Bits are unpacked by bit plane: plane t of four consecutive
 //    dwords (bits 4r + t) is an operand as it stands, d & (0x11111111 << t).
 //
 //    One persistent kernel, 256 x 256 or 128 x 128 output tiles; a wavefront
@@ -47,6 +47,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 #define LDS __attribute__((address_space(3)))
 
 constexpr int MM_W = 8;  // words of a row staged at a time (two 256-bit groups)
+constexpr int MM_PART = 1 << 16;  // words of a row per launch: 2^22 bits
 
 struct MmArgs {
   // Words of a row are staged in two groups of four: group g of chunk c holds
@@ -152,7 +153,8 @@ __device__ __forceinline__ void transpose32x2(uint32_t& a, uint32_t& b) {
 // few different rows of A and B (65536-string table: 1.72 -> 1.67 ms).  Band b
 // of the symmetric table starts at its first row's diagonal; the few tiles of
 // a band below the diagonal are computed like any other (without a mirror),
-// which costs 1 % of the work at 256 rows of tiles.
+// which costs 1 % of the work at 256 rows of tiles.  (Both write the same
+// words, so parts of long rows, which add to C, walk bands of one row.)
 struct TileOrder {
   int64_t b, r;  // band, place within it
 
@@ -199,10 +201,17 @@ struct TileOrder {
   }
 };
 
+// ADD: a later part of long rows, whose parities C takes by XOR.
+template <bool ADD>
+__device__ __forceinline__ void put_word(const MmArgs& a, int64_t row, int64_t word, uint64_t v) {
+  uint64_t* const p = a.C + row * a.ldc + word;
+  *p = ADD ? *p ^ v : v;
+}
+
 // Parities out of a wave's 64 x 32 BJ part at row r0, column c0.  The
 // instruction's first operand holds B's rows, so a lane holds one row of C
 // and its registers are columns: the row words are packed within the lane.
-template <int BJ>
+template <int BJ, bool ADD>
 __device__ __forceinline__ void write_part(const MmArgs& a, const v16f (&acc)[2][BJ], int64_t r0, int64_t c0,
                                            bool mirror) {
   const int lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
@@ -222,7 +231,7 @@ __device__ __forceinline__ void write_part(const MmArgs& a, const v16f (&acc)[2]
         // columns at or beyond n hold the parities of rows that do not exist
         const int64_t left = a.n - wcol * 64;
         const uint64_t v = (uint64_t)d[j] | ((uint64_t)d[j + 1] << 32);
-        a.C[gi * a.ldc + wcol] = left >= 64 ? v : v & ((1ull << left) - 1);
+        put_word<ADD>(a, gi, wcol, left >= 64 ? v : v & ((1ull << left) - 1));
       }
     }
   }
@@ -237,7 +246,7 @@ __device__ __forceinline__ void write_part(const MmArgs& a, const v16f (&acc)[2]
     transpose32x2(x, y);
     swap32(x, y);
     const int64_t gj = c0 + 32 * (j + h) + l32;
-    if (gj < a.n && wcol < a.cw) a.C[gj * a.ldc + wcol] = ((uint64_t)x | ((uint64_t)y << 32)) & keep;
+    if (gj < a.n && wcol < a.cw) put_word<ADD>(a, gj, wcol, ((uint64_t)x | ((uint64_t)y << 32)) & keep);
   }
 }
 
@@ -254,7 +263,7 @@ __device__ __forceinline__ void write_part(const MmArgs& a, const v16f (&acc)[2]
 // LDS as two groups of 256 bits a row, and a fragment (32 rows, this lane
 // half's 128 bits of the group) is one conflict-free 16-byte read for four
 // products.
-template <int WR, int WC, int BJ>
+template <int WR, int WC, int BJ, bool ADD>
 __global__ __launch_bounds__(64 * WR * WC, 2) void gf2mm_kernel(MmArgs a) {
   constexpr int BS = 64 * WR * WC;
   constexpr int TI = 64 * WR, TJ = 32 * BJ * WC;  // tile rows, columns
@@ -380,7 +389,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void gf2mm_kernel(MmArgs a) {
       __syncthreads();
       buf ^= 1;
     }
-    write_part<BJ>(a, acc, rm[0] + wr, rn[0] + wc, a.sym && rm[0] < rn[0]);
+    write_part<BJ, ADD>(a, acc, rm[0] + wr, rn[0] + wc, a.sym && rm[0] < rn[0]);
     rm[0] = rm[1];
     rn[0] = rn[1];
     rm[1] = rm[2];
@@ -581,12 +590,14 @@ __global__ void basis_coeff_kernel(const uint64_t* __restrict__ D, int32_t m, in
 }
 
 template <int WR, int WC, int BJ>
-zx_status launch_tiles(MmArgs a, int per_cu, hipStream_t s) {
+zx_status launch_tiles(MmArgs a, bool add, int per_cu, hipStream_t s) {
   constexpr int TI = 64 * WR, TJ = 32 * BJ * WC;
   a.tm = (int32_t)((a.m + TI - 1) / TI);
   a.tn = (int32_t)((a.n + TJ - 1) / TJ);
   static_assert(TI == TJ, "the symmetric table pairs tile (i, j) with (j, i)");
-  a.bh = a.sym && a.tm < 64 ? 1 : 4;  // below, the tiles under the diagonal cost more than the reuse gives
+  // with few rows of tiles, those under the diagonal cost more than the reuse
+  // gives; added to C, they would count twice
+  a.bh = a.sym && (a.tm < 64 || add) ? 1 : 4;
   a.n_tiles = 0;
   for (int64_t b = 0; b * a.bh < a.tm; ++b) {
     const int64_t h = a.tm - b * a.bh < a.bh ? a.tm - b * a.bh : a.bh;
@@ -602,7 +613,11 @@ zx_status launch_tiles(MmArgs a, int per_cu, hipStream_t s) {
   // persistent workgroups, the same count on every XCD
   const int64_t per = (d->n_cu / 8 > 0 ? d->n_cu / 8 : 1) * per_cu;
   const int64_t g = per < a.per_xcd ? per : a.per_xcd;
-  hipLaunchKernelGGL((gf2mm_kernel<WR, WC, BJ>), dim3((unsigned)(8 * g)), dim3(64 * WR * WC), 0, s, a);
+  // (a kernel of its own for parts that add: asking in the write-out costs 1 %)
+  if (add)
+    hipLaunchKernelGGL((gf2mm_kernel<WR, WC, BJ, true>), dim3((unsigned)(8 * g)), dim3(64 * WR * WC), 0, s, a);
+  else
+    hipLaunchKernelGGL((gf2mm_kernel<WR, WC, BJ, false>), dim3((unsigned)(8 * g)), dim3(64 * WR * WC), 0, s, a);
   ZX_HIP(hipGetLastError());
   return ZX_OK;
 }
@@ -614,7 +629,7 @@ zx_status launch_tiles(MmArgs a, int per_cu, hipStream_t s) {
 // where the large ones leave CUs without a tile (300 x 5000 x 200 bits: 5.5
 // against 6.7 us) or end on a nearly empty round (8000 strings of 300 qubits,
 // 528 large tiles: 23 against 28 us).
-zx_status launch_gf2mm(const MmArgs& a, hipStream_t s) {
+zx_status launch_gf2mm(const MmArgs& a, bool add, hipStream_t s) {
   const ZxDevice* d = zx_device();
   if (!d) return ZX_EDEVICE;
   auto tiles = [&](int64_t e) {
@@ -624,7 +639,7 @@ zx_status launch_gf2mm(const MmArgs& a, hipStream_t s) {
   const int64_t cu = d->n_cu, big = tiles(256);
   const double t_big = 4.0 * (double)((big + cu - 1) / cu);                              // in 128 x 128 tiles
   const double t_small = 1.2 * 2.0 * (double)((tiles(128) + 2 * cu - 1) / (2 * cu));
-  return big < cu || t_small < t_big ? launch_tiles<2, 2, 2>(a, 2, s) : launch_tiles<4, 2, 4>(a, 1, s);
+  return big < cu || t_small < t_big ? launch_tiles<2, 2, 2>(a, add, 2, s) : launch_tiles<4, 2, 4>(a, add, 1, s);
 }
 
 }  // namespace
@@ -633,23 +648,26 @@ zx_status launch_gf2mm(const MmArgs& a, hipStream_t s) {
 zx_status zx_pauli_commute_mfma(const uint64_t* X, const uint64_t* Z, int64_t n, int32_t n_qubits, int64_t ldq,
                                 uint64_t* C, int64_t ldc, hipStream_t s) {
   MmArgs a{};
-  const int qw = (n_qubits + 63) / 64;
-  a.a[0] = X;
-  a.a[1] = Z;
-  a.b[0] = Z;
-  a.b[1] = X;
+  const int qw = (int)(((int64_t)n_qubits + 63) / 64);
   a.lda = a.ldb = ldq;
   a.m = a.n = n;
-  a.kg[0] = a.kg[1] = qw;
   a.cs = 4;
-  a.nch = (qw + 3) / 4;
-  a.last = (n_qubits % 64) ? ((1ull << (n_qubits % 64)) - 1) : ~0ull;
-  a.last_w[0] = a.last_w[1] = qw - 1;
   a.C = C;
   a.ldc = ldc;
   a.cw = (n + 63) / 64;
   a.sym = 1;
-  return launch_gf2mm(a, s);
+  for (int w0 = 0; w0 < qw; w0 += MM_PART / 2) {
+    const int w = qw - w0 < MM_PART / 2 ? qw - w0 : MM_PART / 2;
+    a.a[0] = a.b[1] = X + w0;
+    a.a[1] = a.b[0] = Z + w0;
+    a.kg[0] = a.kg[1] = w;
+    a.nch = (w + 3) / 4;
+    a.last = w0 + w == qw && (n_qubits % 64) ? ((1ull << (n_qubits % 64)) - 1) : ~0ull;
+    a.last_w[0] = a.last_w[1] = w - 1;
+    const zx_status rc = launch_gf2mm(a, w0 > 0, s);
+    if (rc != ZX_OK) return rc;
+  }
+  return ZX_OK;
 }
 
 extern "C" zx_status zx_gf2_matmul(const uint64_t* A, int64_t m, int64_t lda, const uint64_t* B, int64_t n,
@@ -659,32 +677,36 @@ extern "C" zx_status zx_gf2_matmul(const uint64_t* A, int64_t m, int64_t lda, co
   ZX_CHECK_ARG(A && B && C, "null argument");
   ZX_CHECK_ARG(m > 0 && n > 0 && k_bits > 0, "empty product: m=%lld n=%lld k_bits=%d", (long long)m,
                (long long)n, k_bits);
-  const int kw = (k_bits + 63) / 64;
+  const int kw = (int)(((int64_t)k_bits + 63) / 64);
   ZX_CHECK_ARG(lda >= kw && ldb >= kw, "lda/ldb below %d words", kw);
   ZX_CHECK_ARG(ldc >= (n + 63) / 64, "ldc below %lld words", (long long)((n + 63) / 64));
   MmArgs a{};
-  a.a[0] = A;
-  a.a[1] = kw > 4 ? A + 4 : A;
-  a.b[0] = B;
-  a.b[1] = kw > 4 ? B + 4 : B;
   a.lda = lda;
   a.ldb = ldb;
   a.m = m;
   a.n = n;
-  a.kg[0] = kw;
-  a.kg[1] = kw - 4;
   a.cs = MM_W;
-  a.nch = (kw + MM_W - 1) / MM_W;
-  a.last = (k_bits % 64) ? ((1ull << (k_bits % 64)) - 1) : ~0ull;
-  a.last_w[0] = kw - 1;
-  a.last_w[1] = kw - 5;
   a.C = C;
   a.ldc = ldc;
   a.cw = (n + 63) / 64;
   a.sym = 0;
-  zx_status rc = launch_gf2mm(a, s);
-  if (rc == ZX_OK && (flags & ZX_SYNC)) ZX_HIP(hipStreamSynchronize(s));
-  return rc;
+  for (int w0 = 0; w0 < kw; w0 += MM_PART) {
+    const int w = kw - w0 < MM_PART ? kw - w0 : MM_PART;
+    a.a[0] = A + w0;
+    a.a[1] = A + w0 + (w > 4 ? 4 : 0);
+    a.b[0] = B + w0;
+    a.b[1] = B + w0 + (w > 4 ? 4 : 0);
+    a.kg[0] = w;
+    a.kg[1] = w - 4;
+    a.nch = (w + MM_W - 1) / MM_W;
+    a.last = w0 + w == kw && (k_bits % 64) ? ((1ull << (k_bits % 64)) - 1) : ~0ull;
+    a.last_w[0] = w - 1;
+    a.last_w[1] = w - 5;
+    const zx_status rc = launch_gf2mm(a, w0 > 0, s);
+    if (rc != ZX_OK) return rc;
+  }
+  if (flags & ZX_SYNC) ZX_HIP(hipStreamSynchronize(s));
+  return ZX_OK;
 }
 
 extern "C" zx_status zx_phase_pair_product(const uint64_t* A, const uint64_t* B, int64_t ld, int32_t n_terms,

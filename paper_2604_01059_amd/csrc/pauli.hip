@@ -126,7 +126,7 @@ extern "C" zx_status zx_pauli_commute(const uint64_t* X, const uint64_t* Z, int6
   zx_clear_error();
   ZX_CHECK_ARG(X && Z && C, "null argument");
   ZX_CHECK_ARG(n_paulis > 0 && n_qubits > 0, "empty input");
-  const int qw = (n_qubits + 63) / 64;
+  const int qw = (int)(((int64_t)n_qubits + 63) / 64);
   ZX_CHECK_ARG(ld_q >= qw, "ld_q too small");
   const int64_t nwj = (n_paulis + 63) / 64;
   ZX_CHECK_ARG(ld_c >= nwj, "ld_c too small");
@@ -136,9 +136,9 @@ extern "C" zx_status zx_pauli_commute(const uint64_t* X, const uint64_t* Z, int6
                "ZX_PAULI_FORCE_VALU and ZX_PAULI_FORCE_MFMA together");
   // The matrix cores at every size (64 strings of 20 qubits: 5 against 27 us,
   // whose workgroups walk eight row tiles in turn; 512 strings of 1024: 9
-  // against 219 us; 65536: 1.5 against 6.1 ms), as long as a count of up to
-  // 2 n_qubits stays exact beside the accumulators' 2^23.
-  const bool mfma = (flags & ZX_PAULI_FORCE_MFMA) || (!(flags & ZX_PAULI_FORCE_VALU) && n_qubits < (1 << 22));
+  // against 219 us; 65536: 1.5 against 6.1 ms; 5 of 2^22: 19 against 99 ms,
+  // 1024: 17 against 1140 ms).
+  const bool mfma = !(flags & ZX_PAULI_FORCE_VALU);
   if (mfma) {
     zx_status rc = zx_pauli_commute_mfma(X, Z, n_paulis, n_qubits, ld_q, C, ld_c, s);
     if (rc != ZX_OK) return rc;

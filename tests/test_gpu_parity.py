@@ -141,3 +141,27 @@ def test_gf2_matmul_tiles(zx, m, n, k):
     tot = np.bitwise_xor.reduce(F, axis=0)
     want = (np.bitwise_count(U & tot).sum(axis=1) & 1)
     assert np.array_equal(np.bitwise_count(Ch).sum(axis=1) & 1, want)
+
+
+@pytest.mark.parametrize("m,n,k", [(2, 3, (1 << 23) + 1), (3, 2, (1 << 24) + 77), (130, 5, (1 << 22) + 65),
+                                   (3, 140, (1 << 22) - 1)])
+def test_gf2_matmul_long_rows(zx, m, n, k):
+    """Rows whose counts leave the exact range of the fp32 accumulators, with
+    all-ones rows (the largest count) beside random ones."""
+    import torch
+    print("gf2_matmul long case", m, n, k, flush=True)
+    rng = np.random.default_rng(m + n)
+    kw = (k + 63) // 64
+    U = rng.integers(0, 2 ** 64, (m, kw), dtype=np.uint64)
+    F = rng.integers(0, 2 ** 64, (n, kw), dtype=np.uint64)
+    U[0] = F[0] = np.uint64(2 ** 64 - 1)
+    C = zx.gf2_matmul(zx.to_device_words(U), zx.to_device_words(F), k)
+    torch.cuda.synchronize()
+    if k % 64:
+        U[:, -1] &= np.uint64((1 << (k % 64)) - 1)
+    want = np.zeros((m, (n + 63) // 64), np.uint64)
+    for i in range(m):
+        for j in range(n):
+            bit = int(np.bitwise_count(np.bitwise_xor.reduce(U[i] & F[j]))) & 1
+            want[i, j // 64] |= np.uint64(bit << (j % 64))
+    assert np.array_equal(zx.to_host_words(C), want)

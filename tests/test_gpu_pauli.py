@@ -91,3 +91,37 @@ def test_tile_orders(zx, n, q):
     C2 = zx.pauli_commute(dX, dZ, q, flags=zx.ZX_PAULI_FORCE_MFMA)
     torch.cuda.synchronize()
     assert torch.equal(C1, C2)
+
+
+@pytest.mark.parametrize("n,q", [(5, (1 << 22) + 3), (3, (1 << 23) + 64), (200, (1 << 21) + 5)])
+def test_long_strings(zx, n, q):
+    """Strings whose counts (up to 2 q) leave the exact range of the fp32
+    accumulators: both variants and the default, Y on every qubit (the largest counts) and X
+    on every qubit among them."""
+    import torch
+    rng = np.random.default_rng(n)
+    qw = (q + 63) // 64
+    X = rng.integers(0, 2 ** 64, (n, qw), dtype=np.uint64)
+    Z = rng.integers(0, 2 ** 64, (n, qw), dtype=np.uint64)
+    full, last = np.uint64(2 ** 64 - 1), np.uint64((1 << (q % 64 or 64)) - 1)
+    X[0] = Z[0] = X[1] = Z[1] = X[2] = full
+    Z[2] = 0
+    Z[1, 0] -= np.uint64(1)  # an odd count
+    X[:, -1] &= last
+    Z[:, -1] &= last
+    want = np.zeros((n, (n + 63) // 64), np.uint64)
+    pick = range(n) if n < 10 else (0, 1, 2, 64, 130, n - 1)
+    for i in pick:
+        for j in range(n):
+            bit = int(np.bitwise_count(np.bitwise_xor.reduce((X[i] & Z[j]) ^ (Z[i] & X[j])))) & 1
+            want[i, j // 64] |= np.uint64(bit << (j % 64))
+    for variant in VARIANTS + ["auto"]:
+        print("pauli long case", n, q, variant, flush=True)
+        flags = zx.ZX_PAULI_AUTO if variant == "auto" else _flags(zx, variant)
+        C = zx.pauli_commute(zx.to_device_words(X), zx.to_device_words(Z), q, flags=flags)
+        torch.cuda.synchronize()
+        Ch = zx.to_host_words(C)
+        for i in pick:
+            assert np.array_equal(Ch[i], want[i]), (variant, i)
+        assert np.array_equal(np.stack([(Ch[:, j // 64] >> np.uint64(j % 64)) & np.uint64(1) for j in pick]),
+                              np.stack([[(int(Ch[j, i // 64]) >> (i % 64)) & 1 for i in range(n)] for j in pick]))
