@@ -527,6 +527,7 @@ __global__ __launch_bounds__(PP_T) void phase_pair_kernel(const uint64_t* __rest
       s += (uint32_t)((part[v][wv][0] >> lane) & 1) + 2u * (uint32_t)((part[v][wv][1] >> lane) & 1);
     if (s & 1) z = make_float2(-z.y, z.x);
     if (s & 2) z = make_float2(-z.x, -z.y);
+    z = make_float2(z.x + 0.0f, z.y + 0.0f);  // a negative zero would turn the angle of -1 round
     e += m;
   } else {
     for (int k0 = 0; k0 < m; k0 += PP_CHUNK) {

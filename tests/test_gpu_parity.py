@@ -165,3 +165,25 @@ def test_gf2_matmul_long_rows(zx, m, n, k):
             bit = int(np.bitwise_count(np.bitwise_xor.reduce(U[i] & F[j]))) & 1
             want[i, j // 64] |= np.uint64(bit << (j % 64))
     assert np.array_equal(zx.to_host_words(C), want)
+
+
+@pytest.mark.parametrize("phase8", range(8))
+def test_phase_pair_unit_terms_have_positive_zeros(zx, phase8):
+    """A product of unit terms has no negative zero: the angle of a negative
+    real one is pi, as that of a single factor -2 is."""
+    import torch
+    m, n = 5, 130
+    rng = np.random.default_rng(40 + phase8)
+    ka, kb = np.array([0, 4, 0, 4, 0], np.int8), np.array([2, 2, 6, 4, 0], np.int8)
+    A = pack_rows((rng.random((m, n)) < 0.5).astype(np.uint8))
+    B = pack_rows((rng.random((m, n)) < 0.5).astype(np.uint8))
+    print("phase_pair zeros", phase8, flush=True)
+    mo, eo = oph.phase_pair_product(A, B, ka, kb, n, phase8, 0)
+    mg, eg = zx.phase_pair_product(zx.to_device_words(A), zx.to_device_words(B), torch.from_numpy(ka).cuda(),
+                                   torch.from_numpy(kb).cuda(), n, phase8, 0)
+    torch.cuda.synchronize()
+    z = mg.cpu().numpy()
+    _compare(z, eg.cpu().numpy(), mo, eo, 0)
+    assert not np.signbit(z[z == 0]).any()
+    zero = z == 0
+    assert zero.any() == (phase8 % 2 == 0)
