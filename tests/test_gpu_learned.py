@@ -545,3 +545,25 @@ def test_fallback_beside_a_diagram_beyond_the_learned_budget(zx):
     assert all(i.status == 0 and i.n_trace == 0 and i.rank >= 0 for i in info)
     L, G = zx.ZX_POLICY_LEARNED, zx.ZX_POLICY_GREEDY
     assert [i.policy for i in info] == [L, L, G, G, G]
+
+
+@pytest.mark.parametrize("rows", [1, 31, 32, 33, 63, 4064, 4096, 4097, 32736, 32768, 32769, 65601])
+def test_mlp_backward_exact(zx, rows):
+    """Edges of the chunks, staged parts and part count again, with small whole
+    numbers: every product and sum is below 2^24, so fp32 is exact in any
+    order, and one row left out or taken twice shows."""
+    rng = np.random.default_rng(170 + rows)
+    p = np.zeros(omlp.NPARAM, np.float32)
+    W1, b1, w2, _ = omlp.unpack(p)
+    W1[:] = rng.integers(-1, 2, W1.shape)
+    b1[:] = rng.integers(-2, 3, b1.shape)
+    w2[:] = rng.integers(1, 3, w2.shape) * rng.choice([-1, 1], w2.shape)
+    m = make_mlp(zx, p)
+    X = rng.integers(-2, 3, (rows, omlp.IN)).astype(np.float32)
+    X[0] = X[-1] = 1  # no row of zeros at the ends
+    d = rng.choice([-1.0, 1.0], rows).astype(np.float32)
+    print("backward exact rows", rows, flush=True)
+    g = m.backward(torch.from_numpy(bf16_bits(X).view(np.int16)).cuda(), torch.from_numpy(d).cuda()).cpu().numpy()
+    ref = omlp.backward(p, bf16_bits(X), d.astype(np.float64))
+    assert np.abs(ref).max() < 2 ** 22
+    np.testing.assert_array_equal(g, ref.astype(np.float32))
