@@ -37,6 +37,8 @@
 //    whose values are all 2 i^s are counted bit-sliced; with any other term,
 //    one lane per setting, fp32 complex products, renormalised to a power of
 //    two every 8 factors.
+#include <algorithm>
+
 #include "zx_internal.h"
 
 namespace {
@@ -596,9 +598,15 @@ zx_status launch_tiles(MmArgs a, bool add, int per_cu, hipStream_t s) {
   a.tm = (int32_t)((a.m + TI - 1) / TI);
   a.tn = (int32_t)((a.n + TJ - 1) / TJ);
   static_assert(TI == TJ, "the symmetric table pairs tile (i, j) with (j, i)");
-  // with few rows of tiles, those under the diagonal cost more than the reuse
-  // gives; added to C, they would count twice
-  a.bh = a.sym && (a.tm < 64 || add) ? 1 : 4;
+  const ZxDevice* d = zx_device();
+  if (!d) return ZX_EDEVICE;
+  // persistent workgroups, the same count on every XCD
+  const int64_t per = (d->n_cu / 8 > 0 ? d->n_cu / 8 : 1) * per_cu;
+  // Symmetric: with few rows of tiles, those under the diagonal cost more than
+  // the reuse gives; added to C, they would count twice.  Else bands high
+  // enough for an XCD's tiles in flight, or a workgroup's way to its next tile
+  // leads through many (100000 x 1 x 64 bits: 20.6 us with four rows, 9.6 so).
+  a.bh = a.sym ? (a.tm < 64 || add ? 1 : 4) : (int32_t)std::max<int64_t>(4, (per + a.tn - 1) / a.tn);
   a.n_tiles = 0;
   for (int64_t b = 0; b * a.bh < a.tm; ++b) {
     const int64_t h = a.tm - b * a.bh < a.bh ? a.tm - b * a.bh : a.bh;
@@ -609,10 +617,6 @@ zx_status launch_tiles(MmArgs a, bool add, int per_cu, hipStream_t s) {
     zx_set_error("product of %lld x %lld rows has too many tiles", (long long)a.m, (long long)a.n);
     return ZX_ECAPACITY;
   }
-  const ZxDevice* d = zx_device();
-  if (!d) return ZX_EDEVICE;
-  // persistent workgroups, the same count on every XCD
-  const int64_t per = (d->n_cu / 8 > 0 ? d->n_cu / 8 : 1) * per_cu;
   const int64_t g = per < a.per_xcd ? per : a.per_xcd;
   // (a kernel of its own for parts that add: asking in the write-out costs 1 %)
   if (add)

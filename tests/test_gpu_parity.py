@@ -187,3 +187,20 @@ def test_phase_pair_unit_terms_have_positive_zeros(zx, phase8):
     assert not np.signbit(z[z == 0]).any()
     zero = z == 0
     assert zero.any() == (phase8 % 2 == 0)
+
+
+@pytest.mark.parametrize("m,n,k", [(8320, 1, 64), (33000, 130, 200), (20001, 300, 70), (70000, 40, 130)])
+def test_gf2_matmul_tall(zx, m, n, k):
+    """Few columns of tiles: bands of more than four rows of tiles, the last
+    one short."""
+    import torch
+    print("gf2_matmul tall case", m, n, k, flush=True)
+    rng = np.random.default_rng(m + n)
+    kw = (k + 63) // 64
+    U = rng.integers(0, 2 ** 64, (m, kw), dtype=np.uint64)
+    F = rng.integers(0, 2 ** 64, (n, kw), dtype=np.uint64)
+    C = zx.gf2_matmul(zx.to_device_words(U), zx.to_device_words(F), k)
+    torch.cuda.synchronize()
+    if k % 64:
+        U[:, -1] &= np.uint64((1 << (k % 64)) - 1)
+    assert np.array_equal(zx.to_host_words(C), oracle.gf2_matmul(U, F, k))
