@@ -2437,7 +2437,8 @@ __device__ int64_t greedy_cost(uint8_t* arena, uint8_t* lds, const SimpArgs& a, 
   return ok ? cost : INT64_MAX;
 }
 
-template <int BS, bool LEARN>
+// ARENA: the caller's diagrams never fit in LDS, so that path is left out.
+template <int BS, bool LEARN, bool ARENA = false>
 __device__ __forceinline__ void process_diagram(uint8_t* arena, uint8_t* lds, const SimpArgs& a, Shared& sh) {
   ZxHeader* h = (ZxHeader*)arena;
   const int n = uni(h->n), W = uni(h->W);
@@ -2473,8 +2474,13 @@ __device__ __forceinline__ void process_diagram(uint8_t* arena, uint8_t* lds, co
     __syncthreads();
     return;
   }
-  if (lds_adj_bytes(n, W) + aux <= a.lds_cap) run_diagram<BS, true, LEARN>(arena, lds, a, sh);
-  else run_diagram<BS, false, LEARN>(arena, lds, a, sh);
+  if constexpr (!ARENA) {
+    if (lds_adj_bytes(n, W) + aux <= a.lds_cap) {
+      run_diagram<BS, true, LEARN>(arena, lds, a, sh);
+      return;
+    }
+  }
+  run_diagram<BS, false, LEARN>(arena, lds, a, sh);
 }
 
 struct Queue {
@@ -2512,6 +2518,7 @@ struct TeamCtl {
 
 constexpr int64_t TEAM_DK_BYTES = (int64_t)TEAM_MAXW * 64;  // phase increments of up to 8192 rows
 constexpr int64_t TEAM_LDS = 152 * 1024;
+static_assert((int64_t)TEAM_MIN_N * TEAM_MIN_N / 8 > TEAM_LDS, "a team's diagrams run in the arena");
 
 __global__ void team_reset(TeamCtl* t, int8_t* dk) {
   if (threadIdx.x == 0) t->next = 0;
@@ -2595,7 +2602,7 @@ void team_kernel(uint8_t* const* table, int32_t n_graphs, TeamCtl* ctl, SimpArgs
     const int idx = uni(sh.idx);
     __syncthreads();
     if (idx >= n_graphs) break;
-    process_diagram<BS, false>(table[idx], smem_dyn, a, sh);
+    process_diagram<BS, false, true>(table[idx], smem_dyn, a, sh);
   }
   if (threadIdx.x == 0) __hip_atomic_store(&tb->exit, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
