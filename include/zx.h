@@ -208,7 +208,8 @@ zx_status zx_pivot(zx_graph* g, int32_t u, int32_t v, uint32_t flags, hipStream_
  * learned result when its gate2q -- Hadamard edges left plus, with extract,
  * the row additions of the output frontier -- is not above the greedy one,
  * else as the greedy result (the greedy schedule runs again to write it,
- * trace included).  A diagram beyond the learned policy's LDS budget, or
+ * trace included).  A diagram beyond the launch's LDS budget for the learned
+ * policy (7304 spiders; 2048 where the batch has a diagram beyond those), or
  * whose learned run fails on the device, gets the greedy result.
  * zx_graph_info.policy tells which schedule the arena holds.  Not combined
  * with max_rounds or ZX_RESUME (ZX_EINVAL). */
@@ -227,9 +228,10 @@ typedef struct {
 } zx_simplify_opts;
 
 /* Number of kernel variants and a short description of variant id
- * ("bs<threads>-lds<KiB>k", or "by-size": a launch per run of sizes, each
- * with the LDS budget its diagrams need; the default of a greedy batch).  The
- * one-wavefront variant (bs64) runs the
+ * ("bs<threads>-lds<KiB>k", or "by-size", the default of a greedy batch:
+ * planned from its sizes, either a launch per run of sizes, each with the LDS
+ * budget its diagrams need, or one launch on a small budget with the larger
+ * diagrams in device memory).  The one-wavefront variant (bs64) runs the
  * greedy schedule only: with ZX_POLICY_LEARNED it is refused as too small
  * (ZX_ECAPACITY).  Without a tune_id, a batch of up to 256 diagrams of at
  * most 64 spiders takes it; such diagrams without parameters run their
@@ -240,7 +242,7 @@ const char* zx_simplify_variant_name(int32_t id);
 /* Workspace for a batch of n_graphs diagrams. */
 size_t zx_simplify_workspace_bytes(int32_t n_graphs);
 
-/* One persistent launch over all graphs (uploads the batch descriptor into
+/* The planned launches over all graphs (uploads the batch descriptor into
  * ws first, synchronously).  Larger diagrams are scheduled first. */
 zx_status zx_simplify(zx_graph* const* graphs, int32_t n_graphs, const zx_simplify_opts* o,
                       void* ws, size_t ws_bytes, hipStream_t s);
@@ -348,7 +350,7 @@ zx_status zx_pauli_commute(const uint64_t* X, const uint64_t* Z, int64_t n_pauli
  * words at or beyond ceil(n/64) are not written), all device memory.  Bits at
  * or beyond k_bits are ignored; bits beyond n in a row of C are zero.  Runs
  * on the matrix cores: bits enter as FP4 values 0 and 1 and every sum is an
- * exact fp32 count.  flags: ZX_SYNC only.  Asynchronous on s. */
+ * exact fp32 count (of 2^22 bits at most: longer rows take several launches).  flags: ZX_SYNC only.  Asynchronous on s. */
 zx_status zx_gf2_matmul(const uint64_t* A, int64_t m, int64_t lda, const uint64_t* B, int64_t n,
                         int64_t ldb, int32_t k_bits, uint64_t* C, int64_t ldc, uint32_t flags,
                         hipStream_t s);

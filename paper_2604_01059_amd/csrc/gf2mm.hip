@@ -11,8 +11,9 @@
 //    (E2M1) values: a set bit is the code 0b0001 (0.5), the block scale 2^1
 //    makes it 1.0, so every product is 0 or 1 and the fp32 sums (of at most
 //    2^22 bits: longer rows go in parts, a launch each) are exact counts; bit
-//    0 of the count is the parity.  Bits are unpacked by bit plane: plane t of four consecutive
-//    dwords (bits 4r + t) is an operand as it stands, d & (0x11111111 << t).
+//    0 of the count is the parity.  Bits are unpacked by bit plane: plane t of
+//    four consecutive dwords (bits 4r + t) is an operand as it stands,
+//    d & (0x11111111 << t).
 //
 //    One persistent kernel, 256 x 256 or 128 x 128 output tiles; a wavefront
 //    owns 64 x 128 (64 x 64) of a tile: 2 x 4 blocks of 32 x 32, 128 fp32
@@ -45,8 +46,6 @@ namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-
-#define LDS __attribute__((address_space(3)))
 
 constexpr int MM_W = 8;  // words of a row staged at a time (two 256-bit groups)
 constexpr int MM_PART = 1 << 16;  // words of a row per launch: 2^22 bits
@@ -152,7 +151,8 @@ __device__ __forceinline__ void transpose32x2(uint32_t& a, uint32_t& b) {
 
 // Tile order.  Bands of a.bh rows of tiles, each walked column by column, so
 // that the tiles in flight on an XCD (32 workgroups: 4 rows by 8 columns) read
-// few different rows of A and B (65536-string table: 1.72 -> 1.67 ms).  Band b
+// few different rows of A and B (65536-string table under the profiler: 1.72
+// -> 1.67 ms).  Band b
 // of the symmetric table starts at its first row's diagonal; the few tiles of
 // a band below the diagonal are computed like any other (without a mirror),
 // which costs 1 % of the work at 256 rows of tiles.  (Both write the same
@@ -634,8 +634,8 @@ zx_status launch_tiles(MmArgs a, bool add, int per_cu, hipStream_t s) {
 // 256 x 256 tiles (one workgroup of eight waves a CU) or 128 x 128 (two of
 // four waves).  The large ones read half the rows per product and are 1.2
 // times as fast where both fill the chip (4096 x 65536 x 1024 bits: 112
-// against 136 us; 65536-string table: 1.67 against 2.1 ms under the profiler); the small ones
-// where the large ones leave CUs without a tile (300 x 5000 x 200 bits: 5.5
+// against 136 us; 65536-string table under the profiler: 1.67 against 2.1 ms);
+// the small ones where the large ones leave CUs without a tile (300 x 5000 x 200 bits: 5.5
 // against 6.7 us) or end on a nearly empty round (8000 strings of 300 qubits,
 // 528 large tiles: 23 against 28 us).
 zx_status launch_gf2mm(const MmArgs& a, bool add, hipStream_t s) {

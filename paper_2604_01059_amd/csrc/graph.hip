@@ -402,17 +402,15 @@ __device__ bool build_candidates(Ctx<LA>& c, Shared& sh, int kind) {
   return uni(sh.any) != 0;
 }
 
-// One wavefront, after the round's selection (c.sel): the selected
-// spiders' count (sh.cnt, with set_cnt), with lc_trace their trace entries in ascending
-// order, the list of the selected set's words (sh.nsw entries in c.blocked)
-// and of the selected spiders in ascending order (sh.ns entries in
-// c.slist).  The caller's barrier publishes them.
+// One wavefront, after the round's selection (c.sel): the list of the
+// selected set's words (sh.nsw entries in c.blocked) and of the selected
+// spiders in ascending order (sh.ns entries in c.slist).  The caller's barrier
+// publishes them.
 template <bool LA>
-__device__ void list_selected_wave(Ctx<LA>& c, Shared& sh, bool lc_trace, bool set_cnt = true) {
+__device__ void list_selected_wave(Ctx<LA>& c, Shared& sh) {
   const int lane = threadIdx.x & 63;
   LDSP int32_t* sw = (LDSP int32_t*)c.blocked;
   int cnt = 0, ns = 0;
-  const int nt0 = sh.n_trace, round = sh.round;
   for (int j0 = 0; j0 < c.W; j0 += 64) {
     const int j = j0 + lane;
     const uint64_t wd = j < c.W ? c.sel[j] : 0;
@@ -435,13 +433,6 @@ __device__ void list_selected_wave(Ctx<LA>& c, Shared& sh, bool lc_trace, bool s
       const int bit = __ffsll((long long)m) - 1;
       m &= m - 1;
       c.slist[pos] = (int16_t)(64 * j + bit);
-      if (lc_trace && c.trace) {
-        int32_t* e = c.trace + 4 * (int64_t)(nt0 + pos);
-        e[0] = round;
-        e[1] = 0;
-        e[2] = 64 * j + bit;
-        e[3] = -1;
-      }
       ++pos;
     }
     ns += tot;
@@ -449,8 +440,6 @@ __device__ void list_selected_wave(Ctx<LA>& c, Shared& sh, bool lc_trace, bool s
   if (lane == 0) {
     sh.nsw = cnt;
     sh.ns = ns;
-    if (set_cnt) sh.cnt = ns;
-    if (lc_trace && c.trace) sh.n_trace = nt0 + ns;
   }
 }
 
@@ -486,12 +475,13 @@ __device__ __forceinline__ void lc_candidates(Ctx<LA>& c) {
 //
 // Lane l holds words l and l + 64 of the candidates that are left: the first
 // of them is the next spider taken, and its row takes itself and its
-// neighbours out.  So the chain is one dependent row read per spider taken,
-// about six a round whatever the diagram's size; the degree of the spider
-// before is summed while a row is on its way.  Cycles a round at 1024
-// spiders, candidates, selection and sums together: 14.4 k (a pass of its own
-// for each with six barriers, the selection going through all 16 blocks of
-// candidates in turn) -> 7.0 k.
+// neighbours out.  So the chain is one dependent row read per spider taken
+// (about six a round where a tenth of the pairs are edges, hundreds in the
+// first rounds of a large sparse diagram); the degree of the spider before is
+// summed while a row is on its way.  Cycles a round at 1024 spiders,
+// candidates, selection and sums together: 14.4 k (a pass of its own for each
+// with six barriers, the selection going through all 16 blocks of candidates
+// in turn) -> 7.0 k.
 template <int BS, bool LA>
 __device__ void select_lc(Ctx<LA>& c, Shared& sh) {
   if (threadIdx.x < 64) {
@@ -558,7 +548,7 @@ __device__ void select_lc(Ctx<LA>& c, Shared& sh) {
       // the list of the set's words, where a later step walks it
       if (c.pw || ns > SPIDER_MAJOR_MAX || (!LA && c.scr_words < 64)) {
         __builtin_amdgcn_wave_barrier();
-        list_selected_wave(c, sh, false);
+        list_selected_wave(c, sh);
       }
     }
     if (lane == 0) sh.cnt = sh.ns = ns;
@@ -662,7 +652,7 @@ __device__ void select_pivots(Ctx<LA>& c, Shared& sh) {
       sh.n_trace = nt;
     }
     __builtin_amdgcn_wave_barrier();
-    list_selected_wave(c, sh, false, false);  // the lists prepare_round takes
+    list_selected_wave(c, sh);  // the lists prepare_round takes
     __builtin_amdgcn_s_setprio(0);
   }
   __syncthreads();
@@ -1197,9 +1187,7 @@ __device__ __noinline__ void apply_rows_arena(Shared& sh, bool pivot) {
   __syncthreads();
 }
 
-// The same for rows of more than 128 words, which two words a lane do not
-// cover, and for budgets without room for tables.  Rows
-// go in chunks that fit the free LDS: a per-row pass records which selected
+// The same where the free LDS has no room for tables.  Rows go in chunks that fit the free LDS: a per-row pass records which selected
 // spiders the row is adjacent to (hit mask) and updates the row's phase;
 // then a (row, word) pass XORs the hit contributions, staged in LDS when
 // they fit, and drops the selected columns in the same write.  Each row
@@ -1532,7 +1520,7 @@ __device__ bool apply_round(Ctx<LA>& c, Shared& sh, bool pivot) {
         return true;
       }
     }
-    if (uni(sh.ns) <= SPIDER_MAJOR_MAX && c.W <= 128) {
+    if (uni(sh.ns) <= SPIDER_MAJOR_MAX) {
       // a second pass of tables reads the rows again: four groups where they are wanted and fit
       if (uni(sh.ns) > 8 && c.scr_words >= arena_tab_words(c.W, 4)) {
         if (c.W > ARENA_SKIP_W) apply_rows_arena<BS, 4, true>(sh, pivot);
@@ -1545,7 +1533,7 @@ __device__ bool apply_round(Ctx<LA>& c, Shared& sh, bool pivot) {
         return true;
       }
     }
-    if (uni(sh.ns) <= SPIDER_MAJOR_MAX && c.scr_words >= 64) {  // no room for tables, or more than two words a lane
+    if (uni(sh.ns) <= SPIDER_MAJOR_MAX && c.scr_words >= 64) {  // no room for tables
       apply_round_arena<BS>(sh, pivot);
       return true;
     }
@@ -3144,7 +3132,7 @@ const Variant kVariants[] = {
     {256, 96 * 1024, "bs256-lds96k"},   {256, 152 * 1024, "bs256-lds152k"},
     {512, 64 * 1024, "bs512-lds64k"},   {512, 152 * 1024, "bs512-lds152k"},
     {64, 32 * 1024, "bs64-lds32k"},  // one wavefront: greedy schedule, small diagrams
-    {512, 152 * 1024, "by-size"},    // a launch per run of sizes (plan_segments); else as bs512-lds152k
+    {512, 152 * 1024, "by-size"},    // the launches of plan_segments; else as bs512-lds152k
 };
 constexpr int kOneWaveVariant = 6;
 constexpr int kBySizeVariant = 7;

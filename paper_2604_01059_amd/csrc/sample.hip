@@ -7,11 +7,12 @@
 //
 // A wavefront samples a chunk of consecutive shots, a lane one shot at a
 // time; the f rows (fw <= 32 words) of the chunk live in LDS and are written
-// out as one contiguous block when ld_out = fw.  Random numbers are counter-based SplitMix64 (Steele, Lea,
-// Flood, OOPSLA 2014): draw t of shot s is mix64(seed + (s 2^32 + t + 1)
+// out as one contiguous block when ld_out = fw.  Random numbers are
+// counter-based SplitMix64 (Steele, Lea, Flood, OOPSLA 2014): draw t of shot s is mix64(seed + (s 2^32 + t + 1)
 // GAMMA).  Per candidate: one draw for the gap, G = floor(ln U / ln(1 -
 // pmax)), U = ((u >> 11) + 1) 2^-53 (no gap draw when pmax = 1), and one draw
-// v for thinning: fire iff (v >> 11) < floor(p_j / pmax 2^53).  All in fp64.
+// v for thinning: fire iff (v >> 11) < floor(p_j / pmax 2^53).  The values are
+// those of fp64; gap_of decides most gaps in fp32 where that gives the same.
 #include "zx_internal.h"
 
 namespace {
@@ -19,7 +20,10 @@ namespace {
 constexpr int DS_PREP = 1024;     // threads of the preparation
 constexpr int DS_BS = 512;        // threads of the sampler
 constexpr int DS_TAB_MAX = 4096;  // mechanisms whose records go into LDS (64 KiB)
-constexpr int DS_CUS = 256;  // of the card, and its LDS per CU in bytes
+// CUs of the card and LDS bytes a CU, for the launch's shape: asking the runtime
+// for them takes 0.3 of the 11 us of a small call.  With fewer CUs the chunks
+// wait their turn.
+constexpr int DS_CUS = 256;
 constexpr int DS_LDS = 160 * 1024;
 constexpr int DS_CHUNK_WORDS = 1024;  // f words of a wavefront's chunk in LDS (at least a row per lane)
 constexpr int DS_MAX_FW = 32;
@@ -112,8 +116,9 @@ __device__ __forceinline__ int gap_of(uint64_t u, float inv, double log1m, int r
 // decided in fp32 (gap_of).  A mechanism is one 16-byte record (threshold, number
 // of f bits, up to four of them), built in LDS once per workgroup where all
 // fit (TAB), so a candidate costs one load and no chain of three.  16.8 M
-// shots of 193 bits, 641 mechanisms, 0.96 candidates a shot: 497 us with a
-// shot per lane, fp64 logarithms and the chain of loads; now 176 us.
+// shots of 193 bits, 641 mechanisms, 0.96 candidates a shot: 497 us under the
+// profiler with a shot per lane, fp64 logarithms and the chain of loads; now
+// 176 (whole calls without it 445 and 168).
 template <bool TAB>
 __global__ __launch_bounds__(DS_BS) void det_sample_kernel(const int32_t* __restrict__ col_ptr,
                                                            const int32_t* __restrict__ col_idx,

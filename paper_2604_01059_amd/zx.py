@@ -350,7 +350,7 @@ def simplify(graphs, extract=True, tune_id=-1, ws=None, stream=None, policy=ZX_P
 
 
 class Batch:
-    """A prepared batch: one persistent launch per ``run`` (capturable)."""
+    """A prepared batch: the launches of its plan per ``run`` (capturable)."""
 
     def __init__(self, graphs, stream=None):
         import torch
