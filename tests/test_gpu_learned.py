@@ -9,7 +9,7 @@ import torch
 import oracle
 from oracle import mlp as omlp
 from oracle import policy as opol
-from workloads import batch_diagram, make_diagram, single_diagram
+from workloads import batch_diagram, single_diagram
 
 pytestmark = pytest.mark.gpu
 
@@ -533,6 +533,7 @@ def test_fallback_beside_a_diagram_beyond_the_learned_budget(zx):
     both schedules up to 2048 spiders (the 64 KiB budget) and runs the others
     greedily.  Phases of pi/4 leave nothing to rewrite, so both schedules
     cost the same and the learned one is kept wherever it was compared."""
+    from workloads import make_diagram
     m = make_mlp(zx, rand_param(np.random.default_rng(29)))
     sizes = [1000, 2048, 2112, 6500, 7400]
     gs = []
